@@ -277,6 +277,10 @@ int env_int(const char *name, int dflt)
     return atoi(v);
 }
 
+// z-split of a temporal sweep of ts steps: the default one of its own tile shape (a remainder sweep's
+// windows differ from a full one's), or the one that the schedule names.
+int zsplit_of(fdtd_t h, int ts) { return h->tz_default ? h->tz_own[ts] : h->tzchunk; }
+
 template <typename T>
 hipError_t launch_one(fdtd_t h, int kernel, int ts, unsigned *queue)
 {
@@ -286,7 +290,7 @@ hipError_t launch_one(fdtd_t h, int kernel, int ts, unsigned *queue)
         // 16-bit storage is built for the temporal sweep only (ts = 1 for single steps)
         (void)kernel;
         e = fdtd::launch_temporal_step<T>(h->plan.g, fields_of<T>(h, h->cur), fields_of<T>(h, 1 - h->cur), c,
-                                          h->tzchunk, ts, h->tvariant, h->stream, h->nt_stores, queue);
+                                          zsplit_of(h, ts), ts, h->tvariant, h->stream, h->nt_stores, queue);
     } else {
         if (kernel == FDTD_KERNEL_PLAIN)
             return fdtd::launch_plain_step<T>(h->plan.g, fields_of<T>(h, h->cur), c, h->stream);
@@ -295,7 +299,7 @@ hipError_t launch_one(fdtd_t h, int kernel, int ts, unsigned *queue)
                                           h->zchunk, h->variant, h->stream, h->nt_stores);
         else if (kernel == FDTD_KERNEL_TEMPORAL)
             e = fdtd::launch_temporal_step<T>(h->plan.g, fields_of<T>(h, h->cur), fields_of<T>(h, 1 - h->cur), c,
-                                              h->tzchunk, ts, h->tvariant, h->stream, h->nt_stores, queue);
+                                              zsplit_of(h, ts), ts, h->tvariant, h->stream, h->nt_stores, queue);
         else
             e = fdtd::launch_fused_step<T>(h->plan.g, fields_of<T>(h, h->cur), fields_of<T>(h, 1 - h->cur), c,
                                            h->zchunk, h->stream);
@@ -661,18 +665,32 @@ int fdtd_create(int nx, int ny, int nz, double dx, double dt, const fdtd_coef *c
         h->tb = o->storage != FDTD_F64 && !h->ch_arr && h->tvariant == 0 ? 4 : 3;
     if (h->tb > 3)
         h->tvariant = 0;  // one row per wave is built for 1..3 steps per sweep
-    h->tzchunk = env_int("FDTD_TZCHUNKS", 0);
-    if (h->tzchunk <= 0) {
-        // One temporal workgroup per CU, and a workgroup's time is close to proportional to the
-        // planes it marches (its z-chunk plus the 2*tb-1 planes it redoes): pick the split that
-        // minimises waves-of-workgroups x planes per workgroup, chunks of 8 to 384 planes (the
-        // tiles of one XCD drift apart over a long chunk and share fewer halo lines in L2:
-        // 1024^3 ran 3 % faster in 342-plane chunks than in one 1024-plane chunk).
-        const int own = fdtd::temporal_own_rows(h->tb, h->tvariant);
-        const int w = fdtd::temporal_width(h->tvariant);
-        const long long tiles = (long long)((nx + w - 1) / w) * ((ny + own - 1) / own);
-        h->tzchunk = best_zsplit(tiles, nz, 2 * h->tb - 1, 8, device_cus(o->device), kTemporalMaxChunk);
+    // One temporal workgroup per CU, and a workgroup's time is close to proportional to the planes it
+    // marches (its z-chunk plus the 2*ts-1 planes it redoes): pick the split that minimises
+    // waves-of-workgroups x planes per workgroup. States that stream from HBM: chunks of 8 to 384 planes
+    // (the tiles of one XCD drift apart over a long chunk and share fewer halo lines in L2: 1024^3 ran
+    // 3 % faster in 342-plane chunks than in one 1024-plane chunk). The column form, where small
+    // cavities leave CUs idle: down to one plane (64^3, 4 steps: 64 chunks 22 us, 8 chunks 38 us).
+    for (int ts = 1; ts <= 4; ++ts) {
+        long long tiles;
+        int min_planes = 8;
+        if (h->tvariant == 0 && !h->nt_stores) {
+            int ntx, nty;
+            fdtd::column_windows(nx, ny, ts, fdtd::column_waves_of(is16(h->storage), ts, h->ce_arr, h->ch_arr), &ntx,
+                                 &nty);
+            tiles = (long long)ntx * nty;
+            min_planes = 1;
+        } else {
+            const int tv = ts > 3 ? 0 : h->tvariant;
+            const int own = fdtd::temporal_own_rows(ts, tv), w = fdtd::temporal_width(tv);
+            tiles = (long long)((nx + w - 1) / w) * ((ny + own - 1) / own);
+        }
+        h->tz_own[ts] = best_zsplit(tiles, nz, 2 * ts - 1, min_planes, device_cus(o->device), kTemporalMaxChunk);
     }
+    h->tzchunk = env_int("FDTD_TZCHUNKS", 0);
+    h->tz_default = h->tzchunk <= 0;
+    if (h->tz_default)
+        h->tzchunk = h->tz_own[h->tb];
     if (o->stream) {
         h->stream = (hipStream_t)o->stream;
         h->own_stream = false;
@@ -1017,6 +1035,7 @@ void apply_schedule(fdtd_t h, const fdtd_schedule *sc)
         h->tb = sc->tb_steps;
         h->tvariant = sc->variant;
         h->tzchunk = sc->zchunks;
+        h->tz_default = false;
     } else {
         h->tb = 1;
         if (sc->kernel == FDTD_KERNEL_SLAB)

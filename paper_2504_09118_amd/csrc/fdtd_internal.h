@@ -102,13 +102,13 @@ hipError_t launch_slab_step(const Geom &g, const Fields<T> &src, const Fields<T>
                             const Coefs<T> &c, int zchunk, int variant, hipStream_t s, bool nt_stores = true,
                             const SlabExtras *extras = nullptr);
 
-// Temporal step: ts (1..3) leapfrog steps in one sweep; reads src, writes dst.
+// Temporal step: ts (1..4) leapfrog steps in one sweep; reads src, writes dst.
 // Built for FP32, FP16 and BF16 field storage (16-bit fields compute in FP32
 // with FP32 coefficients).
-// nt_stores as for the slab step (honoured for FP32 fields; 16-bit fields always
-// store non-temporally).
-// queue: the solver's two scheduling counters (zero before the launch, zero
-// again after it), used when the tiles are handed out from a queue; may be null.
+// nt_stores: the streamed state is larger than the last-level cache. False selects the
+// column form for variant 0, and default-policy stores for FP32 fields of variant 1.
+// queue: the solver's scheduling counters (zero before the launch, zero again after
+// it), used when the tiles are handed out from a queue; may be null.
 template <typename T>
 hipError_t launch_temporal_step(const Geom &g, const Fields<T> &src, const Fields<T> &dst,
                                 const Coefs<typename Store<T>::C> &c, int zchunk, int ts, int variant,
@@ -116,15 +116,35 @@ hipError_t launch_temporal_step(const Geom &g, const Fields<T> &src, const Field
 
 // MI355X's Infinity Cache (256 MB, the last level before HBM). A sweep whose streamed
 // bytes (both state buffers and the coefficient arrays) fit in it keeps the default
-// store policy, so the next sweep reads the state from the cache; larger states store
-// non-temporally, which leaves L2 to the halo lines neighbouring tiles share.
+// store policy, so the next sweep reads the state from the cache, and temporal steps take
+// the column form; larger states store non-temporally, which leaves L2 to the halo lines
+// neighbouring tiles share.
 constexpr size_t kStreamCacheBytes = (size_t)256 << 20;
 // 32-bit scheduling counters a queue-scheduled temporal launch uses (zero before the
 // launch, zero again after it): one next-tile index per XCD list, the count of finished
 // workgroups and the mask of lists seen empty.
 constexpr int kSchedWords = 10;
+
 int temporal_own_rows(int ts, int variant);
 int temporal_width(int variant);
+
+// The column form of the temporal step (column.h): the same steps and bits, default store policy. It is
+// what a variant-0 temporal step runs for a state that the last-level cache holds (nt_stores false).
+// Rows per lane, waves of a workgroup, x-y windows of a grid.
+constexpr int kColumnRows = 2;
+constexpr int column_waves_of(bool half, int ts, bool ce_arr, bool ch_arr)
+{
+    return ts > 2 && ((ce_arr && ch_arr) || (half && (ce_arr || ch_arr))) ? 12 : 16;
+}
+inline void column_windows(int nx, int ny, int ts, int waves, int *ntx, int *nty)
+{
+    const int sw = 64 - 2 * ts, sr = kColumnRows * waves - 2 * ts;
+    *ntx = nx <= 64 ? 1 : (nx - 2 * ts + sw - 1) / sw;
+    *nty = ny <= kColumnRows * waves ? 1 : (ny - 2 * ts + sr - 1) / sr;
+}
+template <typename T>
+hipError_t launch_column_step(const Geom &g, const Fields<T> &src, const Fields<T> &dst, const Coefs<float> &c,
+                              int zchunk, int ts, hipStream_t s, unsigned *queue);
 
 // One request of a batched temporal launch (FP32 fields, variant-0 tiles).
 struct BatchEntry {

@@ -18,6 +18,8 @@ struct fdtd_solver {
     double scale[3];  // stored component = physical value x scale (1, dy/dx, dz/dx)
     bool aniso;       // d[1] or d[2] differs from dx
     int storage, kernel, tb, device, zchunk, tzchunk, variant, tvariant;
+    int tz_own[5];    // default z-split of a temporal sweep of 1..4 steps
+    bool tz_default;  // no schedule was chosen: each sweep takes its own default split
     hipStream_t stream;
     bool own_stream;
     char *arena;
