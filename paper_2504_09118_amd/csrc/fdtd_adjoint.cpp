@@ -351,12 +351,15 @@ int backward_impl(fdtd_adjoint_t a, double *grad, void *const lam0[3], int lam0_
         int X, Y, Z;
         fdtd::extents(g, q, X, Y, Z);
         const size_t n = (size_t)X * Y * Z;
+        const T *lam[6] = {(const T *)a->adj[cur][0], (const T *)a->adj[cur][1], (const T *)a->adj[cur][2]};
         if (lam0_dtype == FDTD_F64) {
-            e = fdtd::launch_unpack<T, double>(g, q, (const T *)a->adj[cur][q], (double *)s->staging, s->stream);
+            double *out[6] = {(double *)s->staging, (double *)s->staging, (double *)s->staging};
+            e = fdtd::launch_unpack<T, double>(g, q, 1, lam, out, s->stream);
             if (e == hipSuccess)
                 e = hipMemcpyAsync(lam0[q], s->staging, n * sizeof(double), hipMemcpyDeviceToHost, s->stream);
         } else {
-            e = fdtd::launch_unpack<T, float>(g, q, (const T *)a->adj[cur][q], (float *)s->staging, s->stream);
+            float *out[6] = {(float *)s->staging, (float *)s->staging, (float *)s->staging};
+            e = fdtd::launch_unpack<T, float>(g, q, 1, lam, out, s->stream);
             if (e == hipSuccess)
                 e = hipMemcpyAsync(lam0[q], s->staging, n * sizeof(float), hipMemcpyDeviceToHost, s->stream);
         }

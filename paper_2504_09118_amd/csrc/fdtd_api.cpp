@@ -338,19 +338,22 @@ int step_impl(fdtd_t h, long long n, unsigned *queue)
 template <typename S, typename T>
 hipError_t pack_all(fdtd_t h, const void *const src[6], bool staged)
 {
+    const S *p[6];
+    T *a[6], *b[6];
     for (int f = 0; f < 6; ++f) {
-        const S *p = (const S *)src[f];
-        if (staged) {
-            int X, Y, Z;
-            fdtd::extents(h->plan.g, f, X, Y, Z);
-            size_t bytes = (size_t)X * Y * Z * sizeof(S);
-            hipError_t e = hipMemcpyAsync(h->staging, src[f], bytes, hipMemcpyHostToDevice, h->stream);
-            if (e != hipSuccess)
-                return e;
-            p = (const S *)h->staging;
-        }
-        hipError_t e = fdtd::launch_pack<S, T>(h->plan.g, f, p, (T *)h->fld[0][f], (T *)h->fld[1][f], h->stream,
-                                               h->scale[f % 3]);
+        p[f] = (const S *)(staged ? h->staging : src[f]);
+        a[f] = (T *)h->fld[0][f];
+        b[f] = (T *)h->fld[1][f];
+    }
+    if (!staged)
+        return fdtd::launch_pack<S, T>(h->plan.g, 0, 6, p, a, b, h->stream, h->scale);
+    for (int f = 0; f < 6; ++f) {
+        int X, Y, Z;
+        fdtd::extents(h->plan.g, f, X, Y, Z);
+        size_t bytes = (size_t)X * Y * Z * sizeof(S);
+        hipError_t e = hipMemcpyAsync(h->staging, src[f], bytes, hipMemcpyHostToDevice, h->stream);
+        if (e == hipSuccess)
+            e = fdtd::launch_pack<S, T>(h->plan.g, f, 1, p, a, b, h->stream, h->scale);
         if (e != hipSuccess)
             return e;
     }
@@ -360,23 +363,27 @@ hipError_t pack_all(fdtd_t h, const void *const src[6], bool staged)
 template <typename T, typename S>
 hipError_t unpack_all(fdtd_t h, void *const dst[6], bool staged, void *const *boxes, bool scaled)
 {
+    const T *src[6];
+    S *out[6];
+    bool all = true;
+    for (int f = 0; f < 6; ++f) {
+        src[f] = (const T *)boxes[f];
+        out[f] = staged ? (S *)h->staging : (S *)dst[f];
+        all = all && boxes[f];
+    }
+    const double *scale = scaled ? h->scale : nullptr;
+    if (!staged && all)
+        return fdtd::launch_unpack<T, S>(h->plan.g, 0, 6, src, out, h->stream, scale);
     for (int f = 0; f < 6; ++f) {
         int X, Y, Z;
         fdtd::extents(h->plan.g, f, X, Y, Z);
         size_t bytes = (size_t)X * Y * Z * sizeof(S);
-        S *out = staged ? (S *)h->staging : (S *)dst[f];
-        if (!boxes[f]) {
-            hipError_t e = hipMemsetAsync(out, 0, bytes, h->stream);
-            if (e != hipSuccess)
-                return e;
-        } else {
-            hipError_t e = fdtd::launch_unpack<T, S>(h->plan.g, f, (const T *)boxes[f], out, h->stream,
-                                                     scaled ? h->scale[f % 3] : 1.0);
-            if (e != hipSuccess)
-                return e;
-        }
+        hipError_t e = boxes[f] ? fdtd::launch_unpack<T, S>(h->plan.g, f, 1, src, out, h->stream, scale)
+                                : hipMemsetAsync(out[f], 0, bytes, h->stream);
+        if (e != hipSuccess)
+            return e;
         if (staged) {
-            hipError_t e = hipMemcpyAsync(dst[f], h->staging, bytes, hipMemcpyDeviceToHost, h->stream);
+            e = hipMemcpyAsync(dst[f], h->staging, bytes, hipMemcpyDeviceToHost, h->stream);
             if (e != hipSuccess)
                 return e;
             e = hipStreamSynchronize(h->stream);

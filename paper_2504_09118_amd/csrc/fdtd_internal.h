@@ -236,17 +236,19 @@ template <typename T>
 hipError_t launch_coef(const Geom &g, double dx, double dt, const double *eps, const double *mu,
                        T *ce[3], T *ch[3], hipStream_t s, const double *fac = nullptr);
 
-// Dense staggered buffer (type S) -> padded box (type T) for field f, each
-// value multiplied by scale in FP64 and rounded once; writes both destinations
-// (dst2 may be null). E fields get 0 on wall-tangential nodes.
+// Dense staggered arrays (type S) -> padded boxes (type T) for the fields f0 .. f0 + nf - 1 (pointer
+// arrays indexed by field), one launch; each value multiplied by its component's scale (three factors;
+// null: 1) in FP64 and rounded once; writes both destinations (dst2 or its entries may be null). E fields
+// get 0 on wall-tangential nodes.
 template <typename S, typename T>
-hipError_t launch_pack(const Geom &g, int field, const S *src, T *dst, T *dst2, hipStream_t s,
-                       double scale = 1.0);
+hipError_t launch_pack(const Geom &g, int f0, int nf, const S *const *src, T *const *dst, T *const *dst2, hipStream_t s,
+                       const double *scale = nullptr);
 
-// Padded box (type T) -> dense staggered buffer (type S) for field f, each value
-// divided by scale in FP64.
+// Padded boxes (type T) -> dense staggered arrays (type S) for the fields f0 .. f0 + nf - 1, one launch;
+// each value divided by its component's scale in FP64.
 template <typename T, typename S>
-hipError_t launch_unpack(const Geom &g, int field, const T *src, S *dst, hipStream_t s, double scale = 1.0);
+hipError_t launch_unpack(const Geom &g, int f0, int nf, const T *const *src, S *const *dst, hipStream_t s,
+                         const double *scale = nullptr);
 
 // Diagnostics (FP64). partial must hold diag_partial_doubles() doubles.
 size_t diag_partial_doubles();

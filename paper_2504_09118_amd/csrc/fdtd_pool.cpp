@@ -254,9 +254,10 @@ hipError_t init_request(fdtd_pool_t p, Req &r)
         for (int f = 0; f < 6 && e == hipSuccess; ++f) {
             e = hipMemcpyAsync(r.staging, r.fields[f].data(), r.fields[f].size() * sizeof(double),
                                hipMemcpyHostToDevice, p->stream);
+            const double *src[6];
+            for (int q = 0; q < 6; ++q) src[q] = (const double *)r.staging;
             if (e == hipSuccess)
-                e = fdtd::launch_pack<double, float>(g, f, (const double *)r.staging, r.fld[0][f], r.fld[1][f],
-                                                     p->stream);
+                e = fdtd::launch_pack<double, float>(g, f, 1, src, r.fld[0], r.fld[1], p->stream);
         }
         return e;
     }
@@ -557,7 +558,9 @@ hipError_t fetch_fields(fdtd_pool_t p, Req &r, void *const host[6])
         int X, Y, Z;
         fdtd::extents(r.plan.g, f, X, Y, Z);
         const size_t bytes = (size_t)X * Y * Z * sizeof(S);
-        hipError_t e = fdtd::launch_unpack<float, S>(r.plan.g, f, r.fld[r.cur][f], (S *)r.staging, p->fetch_stream);
+        S *out[6];
+        for (int q = 0; q < 6; ++q) out[q] = (S *)r.staging;
+        hipError_t e = fdtd::launch_unpack<float, S>(r.plan.g, f, 1, r.fld[r.cur], out, p->fetch_stream);
         if (e == hipSuccess)
             e = hipMemcpyAsync(host[f], r.staging, bytes, hipMemcpyDeviceToHost, p->fetch_stream);
         if (e == hipSuccess)

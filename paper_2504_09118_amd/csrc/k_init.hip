@@ -10,12 +10,13 @@
 // Wall-tangential E is 0 (PEC) and H = 0. Generating on the device avoids a
 // host round trip when requests are admitted at a high rate.
 #include "fdtd_internal.h"
+#include "plane_index.h"
 #include "storage.h"
 
 namespace fdtd {
 namespace {
 
-constexpr int kBlock = 256;
+constexpr int kBlock = kPlaneBlock;
 
 __device__ __forceinline__ unsigned long long mix64(unsigned long long z)
 {
@@ -25,36 +26,45 @@ __device__ __forceinline__ unsigned long long mix64(unsigned long long z)
 }
 
 template <typename T>
-__global__ void __launch_bounds__(kBlock) k_init_random(Geom g, int field, int X, int Y, long long n,
-                                                        unsigned long long seed, T *dst, T *dst2, double scale)
+struct InitOut {
+    T *a[6], *b[6];
+    double scale[3];
+};
+
+// Component blockIdx.z, one thread per node of a plane (PlaneIndex), planes by blockIdx.y.
+template <typename T>
+__global__ void __launch_bounds__(kBlock) k_init_random(Geom g, PlaneIndex ix, unsigned long long seed, InitOut<T> out)
 {
-    const long long l = (long long)blockIdx.x * kBlock + threadIdx.x;
-    if (l >= n)
+    const int field = blockIdx.z;
+    int X, Y, Z;
+    extents(g, field, X, Y, Z);
+    const unsigned n = (unsigned)X * (unsigned)Y, q = blockIdx.x * kBlock + threadIdx.x;
+    if (q >= n)
         return;
-    const int i = (int)(l % X);
-    const long long r = l / X;
-    const int j = (int)(r % Y);
-    const int k = (int)(r / Y);
-    typename Store<T>::C v = 0;
-    if (field < 3) {
-        bool wall;
-        if (field == 0)
-            wall = j == 0 || j == g.ny || k == 0 || k == g.nz;
-        else if (field == 1)
-            wall = i == 0 || i == g.nx || k == 0 || k == g.nz;
-        else
-            wall = i == 0 || i == g.nx || j == 0 || j == g.ny;
-        if (!wall) {
-            const unsigned long long c = ((unsigned long long)field << 40) + (unsigned long long)l;
-            const unsigned long long z = mix64(seed + (c + 1ull) * 0x9E3779B97F4A7C15ull);
-            const double u = (double)(z >> 11) * 0x1.0p-53;
-            v = to_compute<T>((2.0 * u - 1.0) * scale);  // exact for scale 1
+    const int j = (int)ix.row(q, X, g.nx), i = (int)q - j * X;
+    for (int k = blockIdx.y; k < Z; k += gridDim.y) {
+        const long long l = (long long)k * n + q;
+        typename Store<T>::C v = 0;
+        if (field < 3) {
+            bool wall;
+            if (field == 0)
+                wall = j == 0 || j == g.ny || k == 0 || k == g.nz;
+            else if (field == 1)
+                wall = i == 0 || i == g.nx || k == 0 || k == g.nz;
+            else
+                wall = i == 0 || i == g.nx || j == 0 || j == g.ny;
+            if (!wall) {
+                const unsigned long long c = ((unsigned long long)field << 40) + (unsigned long long)l;
+                const unsigned long long z = mix64(seed + (c + 1ull) * 0x9E3779B97F4A7C15ull);
+                const double u = (double)(z >> 11) * 0x1.0p-53;
+                v = to_compute<T>((2.0 * u - 1.0) * out.scale[field]);  // exact for scale 1
+            }
         }
+        const long long o = g.at(i, j, k);
+        put_elem(out.a[field], g.lo_rec(field), o, v);
+        if (out.b[field])
+            put_elem(out.b[field], g.lo_rec(field), o, v);
     }
-    const long long o = g.at(i, j, k);
-    put_elem(dst, g.lo_rec(field), o, v);
-    if (dst2)
-        put_elem(dst2, g.lo_rec(field), o, v);
 }
 
 }  // namespace
@@ -63,17 +73,14 @@ template <typename T>
 hipError_t launch_init_random(const Geom &g, unsigned long long seed, T *const a[6], T *const b[6], hipStream_t s,
                               const double *scale)
 {
+    InitOut<T> out;
     for (int f = 0; f < 6; ++f) {
-        int X, Y, Z;
-        extents(g, f, X, Y, Z);
-        const long long n = (long long)X * Y * Z;
-        hipLaunchKernelGGL((k_init_random<T>), dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, g,
-                           f, X, Y, n, seed, a[f], b[f], scale ? scale[f % 3] : 1.0);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess)
-            return e;
+        out.a[f] = a[f];
+        out.b[f] = b[f];
     }
-    return hipSuccess;
+    for (int q = 0; q < 3; ++q) out.scale[q] = scale ? scale[q] : 1.0;
+    hipLaunchKernelGGL((k_init_random<T>), plane_grid(g, 6, 1), dim3(kBlock), 0, s, g, plane_index(g), seed, out);
+    return hipGetLastError();
 }
 
 template hipError_t launch_init_random<float>(const Geom &, unsigned long long, float *const[6], float *const[6],
