@@ -344,13 +344,16 @@ int fdtd_destroy(fdtd_t h);
  * device's free memory (and within FDTD_HBM_BUDGET bytes when that is set),
  * else K = ceil(sqrt(2N)), the interval of least memory. Every K gives the
  * same bits.
- * Each forward and recompute step is one slab sweep that also adds the source
- * and (up to 16 probes) records the probes; each reverse step is one fused
- * sweep (mu' = mu - K(Ce lam), the gradient terms, lam' = lam - L(Ch mu'),
- * the probe terms) from one adjoint buffer to the other. Environment aids
- * (none changes the bits): FDTD_ADJ_FUSED = 0 (the one-cell-per-thread
- * reverse kernels, in place), FDTD_ADJ_VARIANT = 0..3 (tile shape of the
- * fused sweep; default 1), FDTD_ADJ_ZCHUNKS (its z-split).
+ * A sweep of the forward and of the recompute also adds the source and records
+ * the probes; a reverse sweep is fused (mu' = mu - K(Ce lam), the gradient
+ * terms, lam' = lam - L(Ch mu'), the probe terms) from one adjoint buffer to
+ * the other. With FP32 storage and up to 64 probes sweeps are in column form:
+ * up to four steps forward, up to two in reverse (scalar Ch); else slab sweeps
+ * of one step (up to 16 probes ride in them, a probe kernel takes more).
+ * Environment aids (none changes the bits): FDTD_ADJ_FUSED = 0 (the
+ * one-cell-per-thread reverse kernels, in place); for the slab form of the
+ * reverse sweep FDTD_ADJ_VARIANT = 0..3 (tile shape; default 1) and
+ * FDTD_ADJ_ZCHUNKS (z-split).
  */
 typedef struct fdtd_adjoint *fdtd_adjoint_t;
 

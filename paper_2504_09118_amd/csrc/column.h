@@ -50,6 +50,28 @@ constexpr int column_waves()
     return column_waves_of(sizeof(S) == 2, TS, CE_ARR, CH_ARR);
 }
 
+// What a driven sweep does beside its steps; an undriven one carries nothing.
+struct NoDrive {
+    static constexpr bool on = false;
+};
+
+// The boxes of an undriven sweep, a pointer each, with ColumnBoxes' accessors (as base and distance they
+// cost the sweep two address additions more per box and plane).
+template <typename S>
+struct FieldBoxes {
+    Fields<S> src, dst;
+    Coefs<float> c;
+    static constexpr long long step = 0;
+    __device__ __forceinline__ const S *read_e(long long, int q) const { return src.f[q]; }
+    __device__ __forceinline__ const S *read_h(long long, int q) const { return src.f[3 + q]; }
+    __device__ __forceinline__ S *write_e(long long, int q) const { return dst.f[q]; }
+    __device__ __forceinline__ S *write_h(long long, int q) const { return dst.f[3 + q]; }
+    __device__ __forceinline__ const float *read_ce(long long, int q) const { return c.ce[q]; }
+    __device__ __forceinline__ const float *read_ch(long long, int q) const { return c.ch[q]; }
+    __device__ __forceinline__ float scalar_ce() const { return c.ce_s; }
+    __device__ __forceinline__ float scalar_ch() const { return c.ch_s; }
+};
+
 constexpr unsigned kDrop = 0x80000000u;      // an offset past every plane: reads 0, stores nothing
 constexpr int kRawBufferWord3 = 0x00020000;  // gfx9 raw buffer: 32-bit data format, no swizzle
 
@@ -69,12 +91,10 @@ __device__ __forceinline__ float left_of(float x)
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x138, 0xf, 0xf, true));
 }
 
-template <typename S, int TS, bool CE_ARR, bool CH_ARR>
-__device__ __forceinline__ void column_tile(const Geom &g, const Fields<S> &src, const Fields<S> &dst,
-                                            const Coefs<float> &c, int kchunk, int ntx, int nty, int tile_x,
-                                            int tile_y, int zc)
+template <typename S, int TS, bool CE_ARR, bool CH_ARR, int kNW, typename Boxes, typename Drive>
+__device__ __forceinline__ void column_tile(const Geom &g, const Boxes &b, int kchunk, int ntx, int nty,
+                                            int tile_x, int tile_y, int zc, const Drive &drive)
 {
-    constexpr int kNW = column_waves<S, TS, CE_ARR, CH_ARR>();
     constexpr int kRows = kNR * kNW;
     typedef float f2 __attribute__((ext_vector_type(2)));
     constexpr bool H16 = sizeof(S) == 2, COMP = Store<S>::comp;
@@ -114,6 +134,21 @@ __device__ __forceinline__ void column_tile(const Geom &g, const Fields<S> &src,
         vc[r] = in ? (unsigned)(i + px * j) * 4u : kDrop;
     }
 
+    // driven: whether this wave holds the source node (own or halo: every copy of it is driven), and which
+    // probes lie in its rows and planes
+    bool has_source = false;
+    unsigned long long probes = 0;
+    int source_plane = 0;
+    if constexpr (Drive::on) {
+        const auto *t = constant(drive.tab);
+        source_plane = t->sk;
+        has_source = t->sf >= 0 && t->sj >= j0 && t->sj < j0 + kNR && t->si >= i - lane && t->si < i - lane + kCols;
+        const bool here = drive.rec && lane < t->np && t->pj[lane] >= j0 && t->pj[lane] < j0 + kNR &&
+                          t->pi[lane] >= i - lane && t->pi[lane] < i - lane + kCols && t->pk[lane] >= kb &&
+                          t->pk[lane] < ke;
+        probes = __ballot(here);
+    }
+
     // Register rings as in k_temporal.hip: role r at phase ph is slot (r + off + ph) mod M, and the plane
     // loop is unrolled M times, so that a value passes to the next stage by a change of name.
     //   E roles: -2 (E prefetched for plane k+2), -1 (E^n at p_1 + 1), s = 0..TS-1 (E of stage s at p_s);
@@ -132,8 +167,8 @@ __device__ __forceinline__ void column_tile(const Geom &g, const Fields<S> &src,
             for (int r = 0; r < kNR; ++r) {
                 RE[m][q][r] = 0.0f;
                 RH[m][q][r] = 0.0f;
-                RC[m][q][r] = CE_ARR ? 0.0f : c.ce_s;
-                RK[m][q][r] = CH_ARR ? 0.0f : c.ch_s;
+                RC[m][q][r] = CE_ARR ? 0.0f : b.scalar_ce();
+                RK[m][q][r] = CH_ARR ? 0.0f : b.scalar_ch();
             }
 #define ES(r, ph) ((((r) + 2 + (ph)) % M + M) % M)
 #define HS(r, ph) ((((r) + 1 + (ph)) % M + M) % M)
@@ -181,30 +216,30 @@ __device__ __forceinline__ void column_tile(const Geom &g, const Fields<S> &src,
         const long long pk1 = up ? pk + P : 0;
         const unsigned nf = up ? fbytes : 0u, nc = up ? cbytes : 0u;
         if constexpr (H16) {
-            for (int q = 0; q < 3; ++q) load16(qe[q], src.f[q] + pk, fbytes);
+            for (int q = 0; q < 3; ++q) load16(qe[q], b.read_e(b.step, q) + pk, fbytes);
             if (COMP)
-                load_rec(qre, src.f[0], pk, cbytes);
+                load_rec(qre, b.read_e(b.step, 0), pk, cbytes);
             decode(RE[ES(0, 0)], qe, qre);
             for (int q = 0; q < 3; ++q) {
-                load16(qe[q], src.f[q] + pk1, nf);
-                load16(qh[q], src.f[3 + q] + pk, fbytes);
+                load16(qe[q], b.read_e(b.step, q) + pk1, nf);
+                load16(qh[q], b.read_h(b.step, q) + pk, fbytes);
             }
             if (COMP) {
-                load_rec(qre, src.f[0], pk1, nc);
-                load_rec(qrh, src.f[3], pk, cbytes);
+                load_rec(qre, b.read_e(b.step, 0), pk1, nc);
+                load_rec(qrh, b.read_h(b.step, 0), pk, cbytes);
             }
         } else {
             for (int q = 0; q < 3; ++q) {
-                load32(RE[ES(0, 0)][q], src.f[q] + pk, fbytes);
-                load32(RE[ES(-1, 0)][q], src.f[q] + pk1, nf);
-                load32(RH[HS(0, 0)][q], src.f[3 + q] + pk, fbytes);
+                load32(RE[ES(0, 0)][q], b.read_e(b.step, q) + pk, fbytes);
+                load32(RE[ES(-1, 0)][q], b.read_e(b.step, q) + pk1, nf);
+                load32(RH[HS(0, 0)][q], b.read_h(b.step, q) + pk, fbytes);
             }
         }
         for (int q = 0; q < 3; ++q) {
             if (CE_ARR)
-                load32(RC[HS(0, 0)][q], c.ce[q] + pk, cbytes);
+                load32(RC[HS(0, 0)][q], b.read_ce(b.step, q) + pk, cbytes);
             if (CH_ARR)
-                load32(RK[HS(0, 0)][q], c.ch[q] + pk, cbytes);
+                load32(RK[HS(0, 0)][q], b.read_ch(b.step, q) + pk, cbytes);
         }
     }
     {
@@ -222,36 +257,44 @@ __device__ __forceinline__ void column_tile(const Geom &g, const Fields<S> &src,
             if (k > kend)
                 break;
             const int par = k & 1;
+            long long pk0 = (long long)k * P;
+            // box addresses are formed anew in each plane: stepped on or kept as loop invariants they would be
+            // spilled (128^3, 4 steps: 48.8 us)
+            long long fs = b.step;
+            if constexpr (Drive::on)
+                __asm__ volatile("" : "+s"(fs));
+            else
+                __asm__ volatile("" : "+s"(pk0));
             // ---- decode the previous prefetch, prefetch the inputs of plane k+1 (E of k+2) ----
             {
                 const bool pv = k + 1 <= kend && k + 1 < nz;
                 const bool pv2 = pv && k + 2 < nz;
-                const long long pk1 = pv ? (long long)(k + 1) * P : 0, pk2 = pv2 ? pk1 + P : 0;
+                const long long pk1 = pk0 + P, pk2 = pk1 + P;  // (planes that do not exist have no bytes)
                 const unsigned nc1 = pv ? cbytes : 0u, nc2 = pv2 ? cbytes : 0u;
                 if constexpr (H16) {
                     decode(RE[ES(-1, ph)], qe, qre);
                     decode(RH[HS(0, ph)], qh, qrh);
                     const unsigned nf1 = pv ? fbytes : 0u, nf2 = pv2 ? fbytes : 0u;
 #pragma unroll
-                    for (int q = 0; q < 3; ++q) load16(qe[q], src.f[q] + pk2, nf2);
+                    for (int q = 0; q < 3; ++q) load16(qe[q], b.read_e(fs, q) + pk2, nf2);
 #pragma unroll
-                    for (int q = 0; q < 3; ++q) load16(qh[q], src.f[3 + q] + pk1, nf1);
+                    for (int q = 0; q < 3; ++q) load16(qh[q], b.read_h(fs, q) + pk1, nf1);
                     if (COMP) {
-                        load_rec(qre, src.f[0], pk2, nc2);
-                        load_rec(qrh, src.f[3], pk1, nc1);
+                        load_rec(qre, b.read_e(fs, 0), pk2, nc2);
+                        load_rec(qrh, b.read_h(fs, 0), pk1, nc1);
                     }
                 } else {
 #pragma unroll
-                    for (int q = 0; q < 3; ++q) load32(RE[ES(-2, ph)][q], src.f[q] + pk2, nc2);
+                    for (int q = 0; q < 3; ++q) load32(RE[ES(-2, ph)][q], b.read_e(fs, q) + pk2, nc2);
 #pragma unroll
-                    for (int q = 0; q < 3; ++q) load32(RH[HS(-1, ph)][q], src.f[3 + q] + pk1, nc1);
+                    for (int q = 0; q < 3; ++q) load32(RH[HS(-1, ph)][q], b.read_h(fs, q) + pk1, nc1);
                 }
 #pragma unroll
                 for (int q = 0; q < 3; ++q) {
                     if (CE_ARR)
-                        load32(RC[HS(-1, ph)][q], c.ce[q] + pk1, nc1);
+                        load32(RC[HS(-1, ph)][q], b.read_ce(fs, q) + pk1, nc1);
                     if (CH_ARR)
-                        load32(RK[HS(-1, ph)][q], c.ch[q] + pk1, nc1);
+                        load32(RK[HS(-1, ph)][q], b.read_ch(fs, q) + pk1, nc1);
                 }
             }
 #pragma unroll
@@ -299,6 +342,47 @@ __device__ __forceinline__ void column_tile(const Geom &g, const Fields<S> &src,
                             }
                         }
                     }
+                    if constexpr (Drive::on) {
+                        // the point source joins its node right after the update, then the probes read E
+                        if (has_source && livep && pp == source_plane) {
+                            const auto *t = constant(drive.tab);
+                            const int f = t->sf, si = t->si, sj = t->sj;
+                            const float w = constant(drive.w)[sp];
+#pragma unroll
+                            for (int r = 0; r < kNR; ++r)
+#pragma unroll
+                                for (int q = 0; q < 3; ++q)
+                                    E[q][r] = f == q && i == si && j0 + r == sj ? E[q][r] + w : E[q][r];
+                        }
+                        const bool mine = livep && pp >= kb && pp < ke;
+                        if (probes && mine) {
+                            for (unsigned long long m = probes; m; m &= m - 1) {
+                                const int q = __builtin_ctzll(m);
+                                const auto *t = constant(drive.tab);
+                                if (t->pk[q] != pp)
+                                    continue;
+                                const int f = t->pf[q], pi = t->pi[q], pj = t->pj[q];
+                                double *rec = drive.rec + (long long)sp * t->np + q;
+#pragma unroll
+                                for (int r = 0; r < kNR; ++r)
+                                    if (own[r] && i == pi && j0 + r == pj)
+                                        *rec = (double)(f == 0 ? E[0][r] : f == 1 ? E[1][r] : E[2][r]);
+                            }
+                        }
+                        // H^{n+sp+1/2} of this plane into its history slot
+                        if (sp < drive.nhist) {
+                            const unsigned n = mine ? fbytes : 0u;
+                            const long long pk = pk0 - sp * P;
+#pragma unroll
+                            for (int q = 0; q < 3; ++q) {
+                                const __amdgpu_buffer_rsrc_t d = plane_rsrc(box_at(drive.hist, fs, 3 * sp + q) + pk, n);
+#pragma unroll
+                                for (int r = 0; r < kNR; ++r)
+                                    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, Hn[q][r]), d,
+                                                                          own[r] ? vc[r] : kDrop, 0, 0);
+                            }
+                        }
+                    }
                     if (sp < TS - 1) {
                         const f2 e = {E[0][0], E[2][0]};
                         sE[par ^ 1][sp + 1][wave][lane] = e;
@@ -306,7 +390,7 @@ __device__ __forceinline__ void column_tile(const Geom &g, const Fields<S> &src,
                         // every lane issues every store: lanes and planes that write nothing drop it
                         const bool wr = livep && pp >= kb;
                         const unsigned nf = wr ? fbytes : 0u;
-                        const long long pk = wr ? (long long)pp * P : 0;
+                        const long long pk = pk0 - sp * P;
                         unsigned vr[kNR], vs[kNR];
 #pragma unroll
                         for (int r = 0; r < kNR; ++r) {
@@ -321,7 +405,8 @@ __device__ __forceinline__ void column_tile(const Geom &g, const Fields<S> &src,
                                 for (int p = 0; p < 3; ++p) {
                                     unsigned hh;
                                     Store<S>::enc2(h ? Hn[p][0] : E[p][0], h ? Hn[p][1] : E[p][1], hh, q[p]);
-                                    const __amdgpu_buffer_rsrc_t d = plane_rsrc(dst.f[3 * h + p] + pk, nf);
+                                    const __amdgpu_buffer_rsrc_t d =
+                                        plane_rsrc((h ? b.write_h(fs, p) : b.write_e(fs, p)) + pk, nf);
                                     __builtin_amdgcn_raw_buffer_store_b16((short)hh, d, vs[0], 0, 0);
                                     __builtin_amdgcn_raw_buffer_store_b16((short)(hh >> 16), d, vs[1], 0, 0);
                                 }
@@ -329,14 +414,16 @@ __device__ __forceinline__ void column_tile(const Geom &g, const Fields<S> &src,
                                 const unsigned w1 = (unsigned)(q[0] >> 8) | ((unsigned)(q[1] >> 8) << 8) |
                                                     ((unsigned)(q[2] >> 8) << 16);
                                 const __amdgpu_buffer_rsrc_t d = plane_rsrc(
-                                    (const char *)dst.f[3 * h] + g.lo_off + kRecBytes * pk, wr ? cbytes : 0u);
+                                    (const char *)(h ? b.write_h(fs, 0) : b.write_e(fs, 0)) + g.lo_off + kRecBytes * pk,
+                                    wr ? cbytes : 0u);
                                 __builtin_amdgcn_raw_buffer_store_b32(w0, d, vr[0], 0, 0);
                                 __builtin_amdgcn_raw_buffer_store_b32(w1, d, vr[1], 0, 0);
                             }
                         } else {
 #pragma unroll
                             for (int q = 0; q < 6; ++q) {
-                                const __amdgpu_buffer_rsrc_t d = plane_rsrc(dst.f[q] + pk, nf);
+                                const __amdgpu_buffer_rsrc_t d = plane_rsrc(
+                                    (q < 3 ? b.write_e(fs, q) : b.write_h(fs, q - 3)) + pk, nf);
                                 const float *x = q < 3 ? E[q % 3] : Hn[q % 3];
                                 if constexpr (H16) {
                                     const unsigned hh = Store<S>::pack2(x[0], x[1]);
@@ -394,8 +481,8 @@ __device__ __forceinline__ void column_tile(const Geom &g, const Fields<S> &src,
 // from the queue.
 template <typename S, int TS, bool CE_ARR, bool CH_ARR>
 __global__ void __launch_bounds__((64 * column_waves<S, TS, CE_ARR, CH_ARR>()))
-    k_column(Geom g, Fields<S> src, Fields<S> dst, Coefs<float> c, int kchunk, int ntx, int nty, int ntiles, int nvb,
-             int remap, int cpx, unsigned *queue)
+    k_column(Geom g, FieldBoxes<S> b, int kchunk, int ntx, int nty, int ntiles, int nvb, int remap, int cpx,
+             unsigned *queue)
 {
     __shared__ int s_v;
     const bool lead = threadIdx.x == 0 && threadIdx.y == 0;
@@ -413,8 +500,8 @@ __global__ void __launch_bounds__((64 * column_waves<S, TS, CE_ARR, CH_ARR>()))
         }
         const int t = tile_of_block(v, ntiles, remap, cpx);
         if (t < ntiles)
-            column_tile<S, TS, CE_ARR, CH_ARR>(g, src, dst, c, kchunk, ntx, nty, t % ntx, (t / ntx) % nty,
-                                               t / (ntx * nty));
+            column_tile<S, TS, CE_ARR, CH_ARR, column_waves<S, TS, CE_ARR, CH_ARR>()>(
+                g, b, kchunk, ntx, nty, t % ntx, (t / ntx) % nty, t / (ntx * nty), NoDrive{});
         if (!queue)
             return;
         __syncthreads();  // the next tile rewrites the LDS this one read last
@@ -437,7 +524,7 @@ hipError_t launch_column(const Geom &g, const Fields<S> &src, const Fields<S> &d
         // serial atomics (64^3: 27 us a sweep through the queue, 24 without)
         const bool direct = !queue || temporal_sched() == 0 || ntiles <= kXcds * cpx;
         const dim3 block(64, waves), grid(direct ? nvb : std::min(ntiles, kXcds * cpx));
-        hipLaunchKernelGGL(kernel, grid, block, 0, s, g, src, dst, c, kchunk, ntx, nty, ntiles, nvb,
+        hipLaunchKernelGGL(kernel, grid, block, 0, s, g, FieldBoxes<S>{src, dst, c}, kchunk, ntx, nty, ntiles, nvb,
                            temporal_sched() == 0 ? xcd_remap() : 2, cpx, direct ? nullptr : queue);
         return hipGetLastError();
     };

@@ -1,13 +1,14 @@
 // Adjoint (reverse-time) gradient of a driven-cavity probe objective with
 // respect to per-cell permittivity (declared and documented in include/fdtd.h).
 //
-// Forward: N single leapfrog steps of the solver, each followed by the point
-// source and the probe reads; the state (E^n, H^{n-1/2}) is copied to a
-// checkpoint every K steps; the steps of the last segment write each H^{n+1/2}
+// Forward: N leapfrog steps of the solver, each followed by the point
+// source and the probe reads, up to four of them in one column sweep (FP32
+// storage and at most 64 probes; else a slab sweep each); the state
+// (E^n, H^{n-1/2}) is copied to a checkpoint every K steps; the steps of the last segment write each H^{n+1/2}
 // straight into a history slot. Backward: for each segment of K steps, last
 // one first, the segment is recomputed from its checkpoint into the history
 // slots (the last one is already there from the forward), then walked in
-// reverse with the adjoint sweeps. With K >= N there is one segment and no
+// reverse with the adjoint sweeps (two steps each in column form). With K >= N there is one segment and no
 // recompute at all. Device memory: ceil(N/K) checkpoints of six boxes,
 // min(K, N) history slots of three H boxes, the adjoint fields (two buffers of
 // six boxes), FP64 dJ/dCe (three boxes) and the FP64 cell gradient.
@@ -20,6 +21,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
+#include <type_traits>
 #include <unordered_set>
 #include <vector>
 
@@ -79,6 +81,7 @@ struct fdtd_adjoint {
     int hist_seg;  // the segment whose H^{n+1/2} the slots hold (-1: none)
     char *mem;
     size_t guard, fbox;
+    size_t clear_bytes;  // both adjoint buffers, gce and gpart
     int *d_pf;
     long long *d_po;
     double *d_rec, *d_J, *d_grad;
@@ -87,6 +90,13 @@ struct fdtd_adjoint {
     fdtd::ProbeList pl;   // the probes as sweep arguments (np = 0 when there are more than fit)
     double *gce[3];
     float *gpart[3];  // FP32 group sums of the gCe terms (FP32 storage), else null
+    // column sweeps (FP32 storage, the probes in the sweep's arguments): the forward and recompute passes,
+    // the reverse pass (scalar Ch as well); z-splits by steps per sweep
+    bool fwd_column, rev_column;
+    int zs_fwd[5], zs_rev[3];
+    int ts_fwd;  // steps of a driven sweep: 4 or 2
+    fdtd::DriveTable *d_tab;  // source and probe nodes for the column sweeps
+    float *d_wave;            // the waveform in the field type
     bool forward_done;
 };
 
@@ -191,15 +201,58 @@ int driven_step(fdtd_adjoint_t a, long long n, double *rec_row, T *const *h_src 
 hipError_t copy_state(fdtd_adjoint_t a, char *dst, bool to_solver)
 {
     fdtd_t s = a->s;
-    for (int q = 0; q < 6; ++q) {
-        char *box = box_of(a, s->fld[s->cur][q]);
-        char *slot = dst + (size_t)q * a->fbox;
-        hipError_t e = to_solver ? hipMemcpyAsync(box, slot, a->fbox, hipMemcpyDeviceToDevice, s->stream)
-                                 : hipMemcpyAsync(slot, box, a->fbox, hipMemcpyDeviceToDevice, s->stream);
+    char *state = box_of(a, s->fld[s->cur][0]);  // six boxes, fbox bytes each (plan_layout)
+    return to_solver ? hipMemcpyAsync(state, dst, 6 * a->fbox, hipMemcpyDeviceToDevice, s->stream)
+                     : hipMemcpyAsync(dst, state, 6 * a->fbox, hipMemcpyDeviceToDevice, s->stream);
+}
+
+// Up to 4 driven steps n .. n + ts - 1 in one column sweep from src to dst; rec: the first step's record
+// row (null: none); hist: the first step's slot, nhist: how many of the steps write theirs.
+hipError_t driven_sweep(fdtd_adjoint_t a, const Fields<float> &src, const Fields<float> &dst, long long n, int ts,
+                        double *rec, float *hist, int nhist)
+{
+    fdtd_t s = a->s;
+    const fdtd::ColumnDrive d{a->d_tab, a->d_wave + n, rec && a->np > 0 ? rec : nullptr, hist, nhist};
+    return fdtd::launch_column_driven(s->plan.g, src, dst, coefs_of<float>(s), a->zs_fwd[ts], ts, s->stream, d);
+}
+
+// Steps of the next driven sweep when left remain: the sweep length chosen at creation, then 2 and 1 (a
+// three-step sweep does not fit the registers: 95 us at 128^3, 79 for the two).
+int driven_steps(const fdtd_adjoint *a, long long left)
+{
+    return left >= a->ts_fwd ? a->ts_fwd : left >= 2 ? 2 : 1;
+}
+
+// The forward in column sweeps of at most 4 steps that end at the checkpoints. In the last segment every
+// H^{n+1/2} goes to its slot; a sweep's last one is also the next sweep's H input, so only the pass's last
+// sweep writes the solver's own H.
+int forward_columns(fdtd_adjoint_t a)
+{
+    fdtd_t s = a->s;
+    const long long nl = (long long)(a->nseg - 1) * a->K;
+    for (long long n = 0; n < a->N;) {
+        hipError_t e = hipSuccess;
+        if (n % a->K == 0 && (e = copy_state(a, a->ckpt + (size_t)(n / a->K) * 6 * a->fbox, false)) != hipSuccess)
+            return fdtd::solver_device_fail(s, e, "checkpoint");
+        const int ts = driven_steps(a, std::min<long long>(a->K - n % a->K, a->N - n));
+        const bool held = n >= nl, last = n + ts == a->N;
+        Fields<float> src = state_of<float>(s), dst = other_of<float>(s);
+        for (int f = 0; f < 3 && held; ++f) {
+            if (n > nl)
+                src.f[3 + f] = hist_slot<float>(a, n - nl - 1, f);
+            if (!last)
+                dst.f[3 + f] = hist_slot<float>(a, n - nl + ts - 1, f);
+        }
+        e = driven_sweep(a, src, dst, n, ts, a->d_rec + (size_t)(n + 1) * a->np,
+                         held ? hist_slot<float>(a, n - nl, 0) : nullptr, !held ? 0 : last ? ts : ts - 1);
         if (e != hipSuccess)
-            return e;
+            return fdtd::solver_device_fail(s, e, "driven sweep");
+        s->cur = 1 - s->cur;
+        s->steps += ts;
+        s->sweeps += 1;
+        n += ts;
     }
-    return hipSuccess;
+    return FDTD_OK;
 }
 
 template <typename T>
@@ -216,7 +269,11 @@ int forward_impl(fdtd_adjoint_t a, double *J)
     // the solver's buffer as the H output, so the solver ends in state N like any forward.
     a->hist_seg = -1;
     const long long nl = (long long)(a->nseg - 1) * a->K;
-    for (long long n = 0; n < a->N; ++n) {
+    if (a->fwd_column) {
+        if (int st = forward_columns(a))
+            return st;
+    }
+    for (long long n = a->fwd_column ? a->N : 0; n < a->N; ++n) {
         if (n % a->K == 0 && (e = copy_state(a, a->ckpt + (size_t)(n / a->K) * 6 * a->fbox, false)) != hipSuccess)
             return fdtd::solver_device_fail(s, e, "checkpoint");
         double *rec = a->d_rec + (size_t)(n + 1) * a->np;
@@ -273,16 +330,8 @@ int backward_impl(fdtd_adjoint_t a, double *grad, void *const lam0[3], int lam0_
         return f;
     };
     adj = adj_of(0);
-    hipError_t e = hipSuccess;
-    for (int b = 0; b < 2; ++b)
-        for (int q = 0; q < 6 && e == hipSuccess; ++q)
-            e = hipMemsetAsync(box_of(a, a->adj[b][q]), 0, a->fbox, s->stream);
-    for (int q = 0; q < 3 && e == hipSuccess; ++q)
-        e = hipMemsetAsync((char *)a->gce[q] - fdtd::kGuardElems * sizeof(double), 0,
-                           (size_t)g.box * sizeof(double), s->stream);
-    for (int q = 0; q < 3 && a->gpart[0] && e == hipSuccess; ++q)
-        e = hipMemsetAsync((char *)a->gpart[q] - fdtd::kGuardElems * sizeof(float), 0,
-                           (size_t)g.box * sizeof(float), s->stream);
+    // the adjoint buffers, gCe and its group sums lie one after the other
+    hipError_t e = hipMemsetAsync(box_of(a, a->adj[0][0]), 0, a->clear_bytes, s->stream);
     if (e == hipSuccess)
         e = fdtd::launch_adj_probe<T>(adj, a->np, a->d_pf, a->d_po, a->d_rec + (size_t)a->N * a->np, s->stream);
     if (e != hipSuccess)
@@ -301,7 +350,26 @@ int backward_impl(fdtd_adjoint_t a, double *grad, void *const lam0[3], int lam0_
             if ((e = copy_state(a, a->ckpt + (size_t)seg * 6 * a->fbox, true)) != hipSuccess)
                 return fdtd::solver_device_fail(s, e, "restore checkpoint");
         }
-        for (long long n = held ? n1 : n0; n < n1; ++n) {
+        if constexpr (std::is_same<T, float>::value) {
+            // the same recompute in column sweeps: the E buffers alternate, every H goes to its slot
+            int b = s->cur;
+            for (long long n = a->fwd_column && !held ? n0 : n1; n < n1;) {
+                const int ts = driven_steps(a, n1 - n);
+                Fields<float> src, dst;
+                for (int f = 0; f < 3; ++f) {
+                    src.f[f] = (float *)s->fld[b][f];
+                    dst.f[f] = (float *)s->fld[1 - b][f];
+                    src.f[3 + f] = n == n0 ? (float *)s->fld[b][3 + f] : slot_h(n - n0 - 1, f);
+                    dst.f[3 + f] = slot_h(n - n0 + ts - 1, f);
+                }
+                e = driven_sweep(a, src, dst, n, ts, nullptr, slot_h(n - n0, 0), ts - 1);
+                if (e != hipSuccess)
+                    return fdtd::solver_device_fail(s, e, "recompute sweep");
+                b = 1 - b;
+                n += ts;
+            }
+        }
+        for (long long n = held || a->fwd_column ? n1 : n0; n < n1; ++n) {
             const long long q = n - n0;
             const int ein = (int)(q & 1) ? 1 - s->cur : s->cur;
             Fields<T> src, dst;
@@ -317,7 +385,29 @@ int backward_impl(fdtd_adjoint_t a, double *grad, void *const lam0[3], int lam0_
                 return fdtd::solver_device_fail(s, e, "recompute step");
         }
         a->hist_seg = seg;
-        for (long long n = n1 - 1; n >= n0; --n) {
+        if constexpr (std::is_same<T, float>::value) {
+            // column sweeps of two steps, the second of an even number (a group of gCe sums closes on a
+            // multiple of kAdjGroup), single ones where the segment's ends leave no pair
+            for (long long n = a->rev_column && fused ? n1 - 1 : n0 - 1; n >= n0;) {
+                const int ts = n % 2 == 1 && n > n0 ? 2 : 1;
+                fdtd::AdjointColumn ac{};
+                ac.hist = slot_h(n - n0, 0);
+                for (int q = 0; q < ts; ++q) {
+                    ac.rec[q] = n - q >= 1 && a->np > 0 ? a->d_rec + (size_t)(n - q) * a->np : nullptr;
+                }
+                ac.gce = a->gce[0];
+                ac.gpart = a->gpart[0];
+                ac.gstep = (char *)a->gce[1] - (char *)a->gce[0];
+                ac.tab = a->d_tab;
+                ac.close = (n - ts + 1) % fdtd::kAdjGroup == 0;
+                e = fdtd::launch_adj_column(g, adj_of(cur), adj_of(1 - cur), c, ac, ts, a->zs_rev[ts], s->stream);
+                if (e != hipSuccess)
+                    return fdtd::solver_device_fail(s, e, "adjoint sweep");
+                cur = 1 - cur;
+                n -= ts;
+            }
+        }
+        for (long long n = a->rev_column && fused ? n0 - 1 : n1 - 1; n >= n0; --n) {
             const T *h[3];
             for (int f = 0; f < 3; ++f) h[f] = slot_h(n - n0, f);
             // the step n with n % kAdjGroup == 0 closes its group (n = 0 closes the last)
@@ -474,6 +564,7 @@ int fdtd_adjoint_create(fdtd_t s, const fdtd_adjoint_problem *p, fdtd_adjoint_t 
     if (grouped)
         off += 3 * pbox;
     const size_t o_grad = off;
+    a->clear_bytes = off - o_adj;
     off += up(ncell * sizeof(double));
     const size_t o_rec = off;
     off += up((size_t)(a->N + 1) * std::max(1, a->np) * sizeof(double));
@@ -483,6 +574,14 @@ int fdtd_adjoint_create(fdtd_t s, const fdtd_adjoint_problem *p, fdtd_adjoint_t 
     off += up((size_t)std::max(1, a->np) * sizeof(int));
     const size_t o_po = off;
     off += up((size_t)std::max(1, a->np) * sizeof(long long));
+    // column sweeps at every size (both passes of 48x40x56 take 0.6 of the slab sweeps' time, of 128^3 0.85,
+    // of 384^3 0.9), where a plane's byte offsets fit 31 bits; the reverse one for one scalar Ch
+    a->fwd_column = s->storage == FDTD_F32 && a->np <= fdtd::kColumnProbes && g.plane < (1LL << 29);
+    a->rev_column = a->fwd_column && !s->ch_arr;
+    const size_t o_tab = off;
+    off += up(sizeof(fdtd::DriveTable));
+    const size_t o_wave = off;
+    off += a->fwd_column ? up((size_t)a->N * sizeof(float)) : 0;
 
     e = hipMalloc((void **)&a->mem, off);
     if (e != hipSuccess) {
@@ -512,12 +611,44 @@ int fdtd_adjoint_create(fdtd_t s, const fdtd_adjoint_problem *p, fdtd_adjoint_t 
             a->pl.pxy[q] = (int)(a->po[q] % g.plane);
         }
     }
+    for (int ts = 1; ts <= 4; ++ts) {
+        a->zs_fwd[ts] = fdtd::column_zsplit(g, ts, fdtd::driven_waves_of(ts, s->ch_arr), s->device);
+        if (ts <= 2)
+            a->zs_rev[ts] = fdtd::column_zsplit(g, ts, fdtd::adjoint_column_waves(ts), s->device);
+    }
+    // A tile of a four-step sweep marches its planes and 8 more. Where the tiles own one plane each, two
+    // sweeps of two steps cost less (64^3: 6.8 us per step, not 7.9; 48x40x56: 6.5, not 7.7); with two
+    // planes four steps are ahead (160x48x48: 9.2 us, not 9.5; 128^3: 19.7, not 23.1).
+    a->ts_fwd = a->zs_fwd[4] >= g.nz ? 2 : 4;
     // history slots cleared once: the cells no sweep writes stay finite (no stencil reads them)
     e = hipMemsetAsync(a->hist, 0, (size_t)a->nslots * 3 * a->fbox, s->stream);
     if (a->np && e == hipSuccess) {
         e = hipMemcpyAsync(a->d_pf, a->pf.data(), a->np * sizeof(int), hipMemcpyHostToDevice, s->stream);
         if (e == hipSuccess)
             e = hipMemcpyAsync(a->d_po, a->po.data(), a->np * sizeof(long long), hipMemcpyHostToDevice, s->stream);
+    }
+    fdtd::DriveTable tab{};
+    std::vector<float> wave;
+    if (a->fwd_column && e == hipSuccess) {
+        a->d_tab = (fdtd::DriveTable *)(a->mem + o_tab);
+        a->d_wave = (float *)(a->mem + o_wave);
+        tab.sf = a->sf;
+        tab.si = p->src_i;
+        tab.sj = p->src_j;
+        tab.sk = p->src_k;
+        tab.np = a->np;
+        for (int q = 0; q < a->np; ++q) {
+            const int *pr = p->probes + 4 * q;
+            tab.pf[q] = pr[0];
+            tab.pi[q] = pr[1];
+            tab.pj[q] = pr[2];
+            tab.pk[q] = pr[3];
+        }
+        wave.assign((size_t)a->N, 0.0f);
+        for (size_t q = 0; q < a->wave.size(); ++q) wave[q] = (float)a->wave[q];
+        e = hipMemcpyAsync(a->d_tab, &tab, sizeof tab, hipMemcpyHostToDevice, s->stream);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(a->d_wave, wave.data(), wave.size() * sizeof(float), hipMemcpyHostToDevice, s->stream);
     }
     if (e == hipSuccess)
         e = hipStreamSynchronize(s->stream);

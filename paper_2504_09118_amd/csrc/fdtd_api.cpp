@@ -502,6 +502,15 @@ int best_zsplit(long long tiles, int nz, int redo, int min_planes, int cus, int 
 
 }  // namespace
 
+namespace fdtd {
+int column_zsplit(const Geom &g, int ts, int waves, int device)
+{
+    int ntx, nty;
+    column_windows(g.nx, g.ny, ts, waves, &ntx, &nty);
+    return best_zsplit((long long)ntx * nty, g.nz, 2 * ts - 1, 1, device_cus(device), kTemporalMaxChunk);
+}
+}  // namespace fdtd
+
 extern "C" {
 
 int fdtd_opts_default(fdtd_opts *o)
@@ -679,20 +688,15 @@ int fdtd_create(int nx, int ny, int nz, double dx, double dt, const fdtd_coef *c
     // 3 % faster in 342-plane chunks than in one 1024-plane chunk). The column form, where small
     // cavities leave CUs idle: down to one plane (64^3, 4 steps: 64 chunks 22 us, 8 chunks 38 us).
     for (int ts = 1; ts <= 4; ++ts) {
-        long long tiles;
-        int min_planes = 8;
         if (h->tvariant == 0 && !h->nt_stores) {
-            int ntx, nty;
-            fdtd::column_windows(nx, ny, ts, fdtd::column_waves_of(is16(h->storage), ts, h->ce_arr, h->ch_arr), &ntx,
-                                 &nty);
-            tiles = (long long)ntx * nty;
-            min_planes = 1;
+            const int waves = fdtd::column_waves_of(is16(h->storage), ts, h->ce_arr, h->ch_arr);
+            h->tz_own[ts] = fdtd::column_zsplit(p.g, ts, waves, o->device);
         } else {
             const int tv = ts > 3 ? 0 : h->tvariant;
             const int own = fdtd::temporal_own_rows(ts, tv), w = fdtd::temporal_width(tv);
-            tiles = (long long)((nx + w - 1) / w) * ((ny + own - 1) / own);
+            const long long tiles = (long long)((nx + w - 1) / w) * ((ny + own - 1) / own);
+            h->tz_own[ts] = best_zsplit(tiles, nz, 2 * ts - 1, 8, device_cus(o->device), kTemporalMaxChunk);
         }
-        h->tz_own[ts] = best_zsplit(tiles, nz, 2 * ts - 1, min_planes, device_cus(o->device), kTemporalMaxChunk);
     }
     h->tzchunk = env_int("FDTD_TZCHUNKS", 0);
     h->tz_default = h->tzchunk <= 0;

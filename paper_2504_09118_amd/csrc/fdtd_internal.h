@@ -142,6 +142,72 @@ inline void column_windows(int nx, int ny, int ts, int waves, int *ntx, int *nty
     *ntx = nx <= 64 ? 1 : (nx - 2 * ts + sw - 1) / sw;
     *nty = ny <= kColumnRows * waves ? 1 : (ny - 2 * ts + sr - 1) / sr;
 }
+// Source and probe nodes of an adjoint problem, in device memory: the column sweeps read it only where a
+// wave holds one of the nodes (as kernel arguments they would occupy scalar registers in every plane).
+constexpr int kColumnProbes = 64;
+struct DriveTable {
+    int sf, si, sj, sk;  // component (< 0: none) and node of the source
+    int np;
+    int pf[kColumnProbes], pi[kColumnProbes], pj[kColumnProbes], pk[kColumnProbes];
+};
+// Data that no kernel writes while it is read, for scalar loads.
+template <typename T>
+__device__ __forceinline__ const __attribute__((address_space(4))) T *constant(const T *p)
+{
+    return (const __attribute__((address_space(4))) T *)(uintptr_t)p;
+}
+// Driven column sweep (FP32, per-node Ce): ts steps from src to dst. w: the steps' source values (device);
+// rec: np values a step, E at the probes after each (null: none); hist: the first box of the first
+// step's history slot, the steps' slots following each other; nhist: how many of the steps write theirs.
+struct ColumnDrive {
+    const DriveTable *tab;
+    const float *w;
+    double *rec;
+    float *hist;
+    int nhist;
+};
+constexpr int driven_waves_of(int ts, bool ch_arr) { return ch_arr && ts > 2 ? 12 : 16; }
+hipError_t launch_column_driven(const Geom &g, const Fields<float> &src, const Fields<float> &dst, const Coefs<float> &c,
+                                int zchunk, int ts, hipStream_t s, const ColumnDrive &drive);
+
+template <typename S>
+__device__ __forceinline__ S *box_at(S *p, long long step, int q)
+{
+    return (S *)((uintptr_t)p + (uintptr_t)(q * step));
+}
+
+// The boxes of an FP32 column sweep that also carries the adjoint's. Boxes lie at equal distances in the
+// arena (Ex .. Hz of a state, the three of a coefficient), so a state is its first box and the distance: a
+// pointer per box would hold more scalar registers than there are beside the drive's and the history's.
+struct ColumnBoxes {
+    const float *se, *sh;   // E and H read
+    float *de, *dh;         // E and H written
+    const float *ce, *ch;   // per-node coefficients, or null
+    long long step;         // bytes from a box to the next
+    float ce_s, ch_s;
+    // component q, given step
+    __device__ __forceinline__ const float *read_e(long long s, int q) const { return box_at(se, s, q); }
+    __device__ __forceinline__ const float *read_h(long long s, int q) const { return box_at(sh, s, q); }
+    __device__ __forceinline__ float *write_e(long long s, int q) const { return box_at(de, s, q); }
+    __device__ __forceinline__ float *write_h(long long s, int q) const { return box_at(dh, s, q); }
+    __device__ __forceinline__ const float *read_ce(long long s, int q) const { return box_at(ce, s, q); }
+    __device__ __forceinline__ const float *read_ch(long long s, int q) const { return box_at(ch, s, q); }
+    __device__ __forceinline__ float scalar_ce() const { return ce_s; }
+    __device__ __forceinline__ float scalar_ch() const { return ch_s; }
+};
+// False when the boxes do not lie like that (every solver's do).
+inline bool column_boxes(const Fields<float> &src, const Fields<float> &dst, const Coefs<float> &c, ColumnBoxes *b)
+{
+    auto gap = [](const void *p, const void *q) { return (long long)((const char *)q - (const char *)p); };
+    const long long f = gap(src.f[0], src.f[1]);
+    *b = ColumnBoxes{src.f[0], src.f[3], dst.f[0], dst.f[3], c.ce[0], c.ch[0], f, c.ce_s, c.ch_s};
+    bool ok = true;
+    for (int q : {0, 1, 3, 4})
+        ok = ok && gap(src.f[q], src.f[q + 1]) == f && gap(dst.f[q], dst.f[q + 1]) == f;
+    for (const auto &k : {c.ce, c.ch})
+        ok = ok && (!k[0] || (gap(k[0], k[1]) == f && gap(k[1], k[2]) == f));
+    return ok;
+}
 template <typename T>
 hipError_t launch_column_step(const Geom &g, const Fields<T> &src, const Fields<T> &dst, const Coefs<float> &c,
                               int zchunk, int ts, hipStream_t s, unsigned *queue);
@@ -219,6 +285,21 @@ template <typename T>
 hipError_t launch_adj_sweep(const Geom &g, const Fields<T> &src, const Fields<T> &dst, const Coefs<T> &c,
                             const T *const hist[3], double *const gce[3], float *const gpart[3], bool close_group,
                             const ProbeList &pl, const double *rec_row, int zchunk, hipStream_t s);
+// The column form of ts (1 or 2) reverse steps (FP32, per-node Ce, scalar Ch): (lam, mu) from src to dst.
+// hist, rec[s]: H^{n-s+1/2} and the probe row of step n - s (null: no probe terms); gpart always, and with
+// close its sums join gce after the last of the steps.
+struct AdjointColumn {
+    const float *hist;     // the first box of step n's slot; the slot of step n - 1 lies before it
+    const double *rec[2];
+    double *gce;           // first boxes; gce's lie gstep bytes apart, gpart's like the fields
+    float *gpart;
+    long long gstep;
+    const DriveTable *tab;
+    bool close;
+};
+constexpr int adjoint_column_waves(int ts) { return ts > 1 ? 12 : 16; }
+hipError_t launch_adj_column(const Geom &g, const Fields<float> &src, const Fields<float> &dst, const Coefs<float> &c,
+                             const AdjointColumn &ac, int ts, int zchunk, hipStream_t s);
 // dJ/d eps per cell (dense x-fastest nx*ny*nz doubles) from dJ/dCe per edge.
 template <typename T>
 hipError_t launch_grad_eps(const Geom &g, const Coefs<T> &c, double *const gce[3], double dx_over_dt, double *out,
