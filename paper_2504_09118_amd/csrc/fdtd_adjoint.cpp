@@ -435,29 +435,32 @@ int backward_impl(fdtd_adjoint_t a, double *grad, void *const lam0[3], int lam0_
     if (e == hipSuccess)
         e = fdtd::launch_grad_eps<T>(g, c, a->gce, s->dx / s->dt, a->d_grad, s->stream);
     const size_t ncell = (size_t)s->nx * s->ny * s->nz;
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(grad, a->d_grad, ncell * sizeof(double), hipMemcpyDeviceToHost, s->stream);
-    for (int q = 0; q < 3 && lam0 && e == hipSuccess; ++q) {
+    size_t bytes[4] = {ncell * sizeof(double)};
+    for (int q = 0; q < 3 && lam0; ++q) {
         int X, Y, Z;
         fdtd::extents(g, q, X, Y, Z);
-        const size_t n = (size_t)X * Y * Z;
+        bytes[1 + q] = (size_t)X * Y * Z * (lam0_dtype == FDTD_F64 ? sizeof(double) : sizeof(float));
+    }
+    fdtd::HostReader &reader = s->reader;
+    if (e == hipSuccess)
+        e = reader.begin(s->device, s->stream, lam0 ? 4 : 1, *std::max_element(bytes, bytes + 4));
+    if (e == hipSuccess)
+        e = reader.add(grad, a->d_grad, bytes[0]);
+    for (int q = 0; q < 3 && lam0 && e == hipSuccess; ++q) {
         const T *lam[6] = {(const T *)a->adj[cur][0], (const T *)a->adj[cur][1], (const T *)a->adj[cur][2]};
         if (lam0_dtype == FDTD_F64) {
             double *out[6] = {(double *)s->staging, (double *)s->staging, (double *)s->staging};
             e = fdtd::launch_unpack<T, double>(g, q, 1, lam, out, s->stream);
-            if (e == hipSuccess)
-                e = hipMemcpyAsync(lam0[q], s->staging, n * sizeof(double), hipMemcpyDeviceToHost, s->stream);
         } else {
             float *out[6] = {(float *)s->staging, (float *)s->staging, (float *)s->staging};
             e = fdtd::launch_unpack<T, float>(g, q, 1, lam, out, s->stream);
-            if (e == hipSuccess)
-                e = hipMemcpyAsync(lam0[q], s->staging, n * sizeof(float), hipMemcpyDeviceToHost, s->stream);
         }
         if (e == hipSuccess)
-            e = hipStreamSynchronize(s->stream);  // staging is reused by the next component
+            e = reader.add(lam0[q], s->staging, bytes[1 + q]);
     }
+    const hipError_t got = reader.finish();
     if (e == hipSuccess)
-        e = hipStreamSynchronize(s->stream);
+        e = got;
     if (e != hipSuccess)
         return fdtd::solver_device_fail(s, e, "adjoint gradient");
     return FDTD_OK;

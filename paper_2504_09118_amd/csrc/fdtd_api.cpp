@@ -374,24 +374,21 @@ hipError_t unpack_all(fdtd_t h, void *const dst[6], bool staged, void *const *bo
     const double *scale = scaled ? h->scale : nullptr;
     if (!staged && all)
         return fdtd::launch_unpack<T, S>(h->plan.g, 0, 6, src, out, h->stream, scale);
+    size_t bytes[6];
     for (int f = 0; f < 6; ++f) {
         int X, Y, Z;
         fdtd::extents(h->plan.g, f, X, Y, Z);
-        size_t bytes = (size_t)X * Y * Z * sizeof(S);
-        hipError_t e = boxes[f] ? fdtd::launch_unpack<T, S>(h->plan.g, f, 1, src, out, h->stream, scale)
-                                : hipMemsetAsync(out[f], 0, bytes, h->stream);
-        if (e != hipSuccess)
-            return e;
-        if (staged) {
-            e = hipMemcpyAsync(dst[f], h->staging, bytes, hipMemcpyDeviceToHost, h->stream);
-            if (e != hipSuccess)
-                return e;
-            e = hipStreamSynchronize(h->stream);
-            if (e != hipSuccess)
-                return e;
-        }
+        bytes[f] = (size_t)X * Y * Z * sizeof(S);
     }
-    return hipSuccess;
+    hipError_t e = staged ? h->reader.begin(h->device, h->stream, 6, *std::max_element(bytes, bytes + 6)) : hipSuccess;
+    for (int f = 0; f < 6 && e == hipSuccess; ++f) {
+        e = boxes[f] ? fdtd::launch_unpack<T, S>(h->plan.g, f, 1, src, out, h->stream, scale)
+                     : hipMemsetAsync(out[f], 0, bytes[f], h->stream);
+        if (staged && e == hipSuccess)
+            e = h->reader.add(dst[f], h->staging, bytes[f]);
+    }
+    const hipError_t got = staged ? h->reader.finish() : hipSuccess;
+    return e != hipSuccess ? e : got;
 }
 
 int set_fields_common(fdtd_t h, const void *const src[6], int dtype, bool staged)

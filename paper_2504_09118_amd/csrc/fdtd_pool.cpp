@@ -35,6 +35,7 @@
 
 #include "fdtd.h"
 #include "fdtd_internal.h"
+#include "host_read.h"
 
 using fdtd::BatchEntry;
 using fdtd::Geom;
@@ -175,6 +176,8 @@ struct fdtd_pool {
     uint32_t magic;
     int device, tb, max_active, backfill;
     hipStream_t stream, fetch_stream;
+    std::mutex fetch_mu;  // one fetch at a time: the link is what it waits for
+    fdtd::HostReader reader;
     bool own_stream;
     char *arena, *base;
     bool own_arena;
@@ -554,21 +557,23 @@ void free_pool(fdtd_pool_t p)
 template <typename S>
 hipError_t fetch_fields(fdtd_pool_t p, Req &r, void *const host[6])
 {
+    std::lock_guard<std::mutex> lk(p->fetch_mu);
+    size_t bytes[6];
     for (int f = 0; f < 6; ++f) {
         int X, Y, Z;
         fdtd::extents(r.plan.g, f, X, Y, Z);
-        const size_t bytes = (size_t)X * Y * Z * sizeof(S);
-        S *out[6];
-        for (int q = 0; q < 6; ++q) out[q] = (S *)r.staging;
-        hipError_t e = fdtd::launch_unpack<float, S>(r.plan.g, f, 1, r.fld[r.cur], out, p->fetch_stream);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(host[f], r.staging, bytes, hipMemcpyDeviceToHost, p->fetch_stream);
-        if (e == hipSuccess)
-            e = hipStreamSynchronize(p->fetch_stream);
-        if (e != hipSuccess)
-            return e;
+        bytes[f] = (size_t)X * Y * Z * sizeof(S);
     }
-    return hipSuccess;
+    S *out[6];
+    for (int q = 0; q < 6; ++q) out[q] = (S *)r.staging;
+    hipError_t e = p->reader.begin(p->device, p->fetch_stream, 6, *std::max_element(bytes, bytes + 6));
+    for (int f = 0; f < 6 && e == hipSuccess; ++f) {
+        e = fdtd::launch_unpack<float, S>(r.plan.g, f, 1, r.fld[r.cur], out, p->fetch_stream);
+        if (e == hipSuccess)
+            e = p->reader.add(host[f], r.staging, bytes[f]);
+    }
+    const hipError_t got = p->reader.finish();
+    return e != hipSuccess ? e : got;
 }
 
 Req *find_req(fdtd_pool_t p, long long id)

@@ -9,6 +9,7 @@
 
 #include "fdtd.h"
 #include "fdtd_internal.h"
+#include "host_read.h"
 
 struct fdtd_solver {
     uint32_t magic;
@@ -37,6 +38,7 @@ struct fdtd_solver {
     int cur;
     long long steps, sweeps;
     bool failed, fields_set;
+    fdtd::HostReader reader;
 };
 
 namespace fdtd {
