@@ -29,6 +29,8 @@
 
 #include <algorithm>
 
+#include <type_traits>
+
 #include "fdtd_internal.h"
 #include "storage.h"
 #include "tile_queue.h"
@@ -479,8 +481,8 @@ __device__ __forceinline__ void column_tile(const Geom &g, const Boxes &b, int k
 
 // One workgroup per tile (queue null, in the order remap names), or one workgroup per CU taking tiles
 // from the queue.
-template <typename S, int TS, bool CE_ARR, bool CH_ARR>
-__global__ void __launch_bounds__((64 * column_waves<S, TS, CE_ARR, CH_ARR>()))
+template <typename S, int TS, bool CE_ARR, bool CH_ARR, int kNW>
+__global__ void __launch_bounds__(64 * kNW, (kNW != kNarrowWaves ? 1 : column_narrow_pairs(TS, CE_ARR, CH_ARR) ? 4 : 2))
     k_column(Geom g, FieldBoxes<S> b, int kchunk, int ntx, int nty, int ntiles, int nvb, int remap, int cpx,
              unsigned *queue)
 {
@@ -500,7 +502,7 @@ __global__ void __launch_bounds__((64 * column_waves<S, TS, CE_ARR, CH_ARR>()))
         }
         const int t = tile_of_block(v, ntiles, remap, cpx);
         if (t < ntiles)
-            column_tile<S, TS, CE_ARR, CH_ARR, column_waves<S, TS, CE_ARR, CH_ARR>()>(
+            column_tile<S, TS, CE_ARR, CH_ARR, kNW>(
                 g, b, kchunk, ntx, nty, t % ntx, (t / ntx) % nty, t / (ntx * nty), NoDrive{});
         if (!queue)
             return;
@@ -521,21 +523,25 @@ hipError_t launch_column(const Geom &g, const Fields<S> &src, const Fields<S> &d
         column_windows(g.nx, g.ny, TS, waves, &ntx, &nty);
         const int ntiles = ntx * nty * nzc, nvb = (ntiles + kXcds - 1) / kXcds * kXcds;
         // with a CU for every tile there is nothing to hand out: a workgroup per tile saves the queue's
-        // serial atomics (64^3: 27 us a sweep through the queue, 24 without)
-        const bool direct = !queue || temporal_sched() == 0 || ntiles <= kXcds * cpx;
+        // serial atomics (64^3: 27 us a sweep through the queue, 24 without); narrow workgroups are two a CU
+        const bool direct = !queue || temporal_sched() == 0 || ntiles <= kXcds * cpx || waves == kNarrowWaves;
         const dim3 block(64, waves), grid(direct ? nvb : std::min(ntiles, kXcds * cpx));
         hipLaunchKernelGGL(kernel, grid, block, 0, s, g, FieldBoxes<S>{src, dst, c}, kchunk, ntx, nty, ntiles, nvb,
                            temporal_sched() == 0 ? xcd_remap() : 2, cpx, direct ? nullptr : queue);
         return hipGetLastError();
     };
     const bool cea = c.ce[0] != nullptr, cha = c.ch[0] != nullptr;
-    if (cea && cha)
-        return go(k_column<S, TS, true, true>, column_waves<S, TS, true, true>());
-    if (cha)
-        return go(k_column<S, TS, false, true>, column_waves<S, TS, false, true>());
-    if (cea)
-        return go(k_column<S, TS, true, false>, column_waves<S, TS, true, false>());
-    return go(k_column<S, TS, false, false>, column_waves<S, TS, false, false>());
+    auto pick = [&](auto ce, auto ch) {
+        constexpr bool CE = decltype(ce)::value, CH = decltype(ch)::value;
+        constexpr int wide = column_waves<S, TS, CE, CH>();
+        if constexpr (column_has_narrow(sizeof(S) == 2))
+            if (column_waves_for(g, TS, wide, column_narrow_pairs(TS, CE, CH), nzc, kXcds * cpx) == kNarrowWaves)
+                return go(k_column<S, TS, CE, CH, kNarrowWaves>, kNarrowWaves);
+        return go(k_column<S, TS, CE, CH, wide>, wide);
+    };
+    using yes = std::true_type;
+    using no = std::false_type;
+    return cea && cha ? pick(yes{}, yes{}) : cha ? pick(no{}, yes{}) : cea ? pick(yes{}, no{}) : pick(no{}, no{});
 }
 
 }  // namespace

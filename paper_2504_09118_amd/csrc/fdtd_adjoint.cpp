@@ -615,9 +615,9 @@ int fdtd_adjoint_create(fdtd_t s, const fdtd_adjoint_problem *p, fdtd_adjoint_t 
         }
     }
     for (int ts = 1; ts <= 4; ++ts) {
-        a->zs_fwd[ts] = fdtd::column_zsplit(g, ts, fdtd::driven_waves_of(ts, s->ch_arr), s->device);
+        a->zs_fwd[ts] = fdtd::column_zsplit(g, ts, fdtd::driven_waves_of(ts, s->ch_arr), false, false, s->device);
         if (ts <= 2)
-            a->zs_rev[ts] = fdtd::column_zsplit(g, ts, fdtd::adjoint_column_waves(ts), s->device);
+            a->zs_rev[ts] = fdtd::column_zsplit(g, ts, fdtd::adjoint_column_waves(ts), false, false, s->device);
     }
     // A tile of a four-step sweep marches its planes and 8 more. Where the tiles own one plane each, two
     // sweeps of two steps cost less (64^3: 6.8 us per step, not 7.9; 48x40x56: 6.5, not 7.7); with two

@@ -500,11 +500,23 @@ int best_zsplit(long long tiles, int nz, int redo, int min_planes, int cus, int 
 }  // namespace
 
 namespace fdtd {
-int column_zsplit(const Geom &g, int ts, int waves, int device)
+int column_zsplit(const Geom &g, int ts, int wide, bool narrow, bool pairs, int device)
 {
-    int ntx, nty;
-    column_windows(g.nx, g.ny, ts, waves, &ntx, &nty);
-    return best_zsplit((long long)ntx * nty, g.nz, 2 * ts - 1, 1, device_cus(device), kTemporalMaxChunk);
+    const int cus = device_cus(device);
+    double best = -1.0;
+    int zc_best = 1;
+    for (int zc = 1; zc <= g.nz; ++zc) {
+        if ((g.nz + zc - 1) / zc > kTemporalMaxChunk && zc < g.nz)
+            continue;
+        double cost = column_cost(g, ts, wide, pairs, zc, cus);
+        if (narrow)
+            cost = std::min(cost, column_cost(g, ts, kNarrowWaves, pairs, zc, cus));
+        if (best < 0 || cost < best) {
+            best = cost;
+            zc_best = zc;
+        }
+    }
+    return zc_best;
 }
 }  // namespace fdtd
 
@@ -683,11 +695,13 @@ int fdtd_create(int nx, int ny, int nz, double dx, double dt, const fdtd_coef *c
     // waves-of-workgroups x planes per workgroup. States that stream from HBM: chunks of 8 to 384 planes
     // (the tiles of one XCD drift apart over a long chunk and share fewer halo lines in L2: 1024^3 ran
     // 3 % faster in 342-plane chunks than in one 1024-plane chunk). The column form, where small
-    // cavities leave CUs idle: down to one plane (64^3, 4 steps: 64 chunks 22 us, 8 chunks 38 us).
+    // cavities leave CUs idle: down to one plane (32^3, 4 steps: 32 chunks 14 us, 8 chunks 18 us).
     for (int ts = 1; ts <= 4; ++ts) {
         if (h->tvariant == 0 && !h->nt_stores) {
-            const int waves = fdtd::column_waves_of(is16(h->storage), ts, h->ce_arr, h->ch_arr);
-            h->tz_own[ts] = fdtd::column_zsplit(p.g, ts, waves, o->device);
+            const bool half = is16(h->storage), ce = h->ce_arr, ch = h->ch_arr;
+            h->tz_own[ts] = fdtd::column_zsplit(p.g, ts, fdtd::column_waves_of(half, ts, ce, ch),
+                                                fdtd::column_has_narrow(half), fdtd::column_narrow_pairs(ts, ce, ch),
+                                                o->device);
         } else {
             const int tv = ts > 3 ? 0 : h->tvariant;
             const int own = fdtd::temporal_own_rows(ts, tv), w = fdtd::temporal_width(tv);

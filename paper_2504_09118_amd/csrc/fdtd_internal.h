@@ -142,6 +142,31 @@ inline void column_windows(int nx, int ny, int ts, int waves, int *ntx, int *nty
     *ntx = nx <= 64 ? 1 : (nx - 2 * ts + sw - 1) / sw;
     *nty = ny <= kColumnRows * waves ? 1 : (ny - 2 * ts + sr - 1) / sr;
 }
+// A cavity too small to give every CU a full workgroup takes workgroups of 8 waves (FP32): a plane's chain of
+// stages and barriers is shorter with two waves per SIMD than with four. Per plane of a full workgroup,
+// measured: 0.7 with a workgroup per CU, 0.9 with two (32^3, 4 steps: 19.7 us, narrow 14.0; 64^3 22.5 and
+// 17.4; at 128^3, where the wide windows fill the chip, 43 and 50).
+constexpr int kNarrowWaves = 8;
+constexpr bool column_has_narrow(bool half) { return !half; }
+// Whether two narrow workgroups fit a CU's registers.
+constexpr bool column_narrow_pairs(int ts, bool ce_arr, bool ch_arr) { return !(ts > 2 && ce_arr && ch_arr); }
+// Time of a sweep in planes of a full workgroup.
+inline double column_cost(const Geom &g, int ts, int waves, bool pairs, int zchunk, int cus)
+{
+    int ntx, nty;
+    column_windows(g.nx, g.ny, ts, waves, &ntx, &nty);
+    const long long kc = (g.nz + zchunk - 1) / zchunk, tiles = (long long)ntx * nty * ((g.nz + kc - 1) / kc);
+    const long long rounds = (tiles + cus - 1) / cus;
+    const double t = waves != kNarrowWaves ? (double)rounds : rounds == 1 || !pairs ? 0.7 * rounds : 0.9 * ((rounds + 1) / 2);
+    return t * (double)(kc + 2 * ts - 1);
+}
+// Waves of a workgroup at a z-split: wide, or kNarrowWaves where that costs less.
+inline int column_waves_for(const Geom &g, int ts, int wide, bool pairs, int zchunk, int cus)
+{
+    return column_cost(g, ts, kNarrowWaves, pairs, zchunk, cus) < column_cost(g, ts, wide, pairs, zchunk, cus)
+               ? kNarrowWaves
+               : wide;
+}
 // Source and probe nodes of an adjoint problem, in device memory: the column sweeps read it only where a
 // wave holds one of the nodes (as kernel arguments they would occupy scalar registers in every plane).
 constexpr int kColumnProbes = 64;
