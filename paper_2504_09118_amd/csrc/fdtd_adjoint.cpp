@@ -577,7 +577,7 @@ int fdtd_adjoint_create(fdtd_t s, const fdtd_adjoint_problem *p, fdtd_adjoint_t 
     off += up((size_t)std::max(1, a->np) * sizeof(int));
     const size_t o_po = off;
     off += up((size_t)std::max(1, a->np) * sizeof(long long));
-    // column sweeps at every size (both passes of 48x40x56 take 0.6 of the slab sweeps' time, of 128^3 0.85,
+    // column sweeps at every size (both passes of 48x40x56 take 0.4 of the slab sweeps' time, of 128^3 0.85,
     // of 384^3 0.9), where a plane's byte offsets fit 31 bits; the reverse one for one scalar Ch
     a->fwd_column = s->storage == FDTD_F32 && a->np <= fdtd::kColumnProbes && g.plane < (1LL << 29);
     a->rev_column = a->fwd_column && !s->ch_arr;
@@ -615,14 +615,16 @@ int fdtd_adjoint_create(fdtd_t s, const fdtd_adjoint_problem *p, fdtd_adjoint_t 
         }
     }
     for (int ts = 1; ts <= 4; ++ts) {
-        a->zs_fwd[ts] = fdtd::column_zsplit(g, ts, fdtd::driven_waves_of(ts, s->ch_arr), false, false, s->device);
+        a->zs_fwd[ts] = fdtd::column_zsplit(g, ts, fdtd::driven_waves_of(ts, s->ch_arr), true,
+                                           fdtd::driven_narrow_pairs(ts), s->device);
         if (ts <= 2)
-            a->zs_rev[ts] = fdtd::column_zsplit(g, ts, fdtd::adjoint_column_waves(ts), false, false, s->device);
+            a->zs_rev[ts] = fdtd::column_zsplit(g, ts, fdtd::adjoint_column_waves(ts), true,
+                                               fdtd::adjoint_narrow_pairs(ts), s->device);
     }
-    // A tile of a four-step sweep marches its planes and 8 more. Where the tiles own one plane each, two
-    // sweeps of two steps cost less (64^3: 6.8 us per step, not 7.9; 48x40x56: 6.5, not 7.7); with two
-    // planes four steps are ahead (160x48x48: 9.2 us, not 9.5; 128^3: 19.7, not 23.1).
-    a->ts_fwd = a->zs_fwd[4] >= g.nz ? 2 : 4;
+    // A tile of a four-step sweep marches its planes and 7 more. Where tiles own three planes or fewer, two
+    // sweeps of two steps cost less or the same (48x40x56: 4.9 us per step, not 5.6; 64^3: 5.7, not 6.3; 96^3:
+    // 10.0, not 10.6); beyond, four steps are ahead (112^3: 15.1, not 16.1; 128^3: 19.5, not 22.8).
+    a->ts_fwd = 3LL * a->zs_fwd[4] >= g.nz ? 2 : 4;
     // history slots cleared once: the cells no sweep writes stay finite (no stencil reads them)
     e = hipMemsetAsync(a->hist, 0, (size_t)a->nslots * 3 * a->fbox, s->stream);
     if (a->np && e == hipSuccess) {

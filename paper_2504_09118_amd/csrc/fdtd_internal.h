@@ -192,6 +192,7 @@ struct ColumnDrive {
     int nhist;
 };
 constexpr int driven_waves_of(int ts, bool ch_arr) { return ch_arr && ts > 2 ? 12 : 16; }
+constexpr bool driven_narrow_pairs(int ts) { return ts <= 2; }
 hipError_t launch_column_driven(const Geom &g, const Fields<float> &src, const Fields<float> &dst, const Coefs<float> &c,
                                 int zchunk, int ts, hipStream_t s, const ColumnDrive &drive);
 
@@ -323,6 +324,7 @@ struct AdjointColumn {
     bool close;
 };
 constexpr int adjoint_column_waves(int ts) { return ts > 1 ? 12 : 16; }
+constexpr bool adjoint_narrow_pairs(int ts) { return ts == 1; }
 hipError_t launch_adj_column(const Geom &g, const Fields<float> &src, const Fields<float> &dst, const Coefs<float> &c,
                              const AdjointColumn &ac, int ts, int zchunk, hipStream_t s);
 // dJ/d eps per cell (dense x-fastest nx*ny*nz doubles) from dJ/dCe per edge.

@@ -10,8 +10,8 @@
 // What bounds it: at 128^3 (two steps, 75 us; the slab sweep 43 us for one) 310 MB cross the last-level
 // cache's edge at 4.1 TB/s, the window's halo among them (60 of 64 columns, 20 of 24 rows own); a plane's
 // three barriers and its scalar address work keep it from the 11 TB/s that a copy there reaches. A sweep of
-// one step takes 71 us. 128^3, 200 steps with 2 probes: 9.2 ms, slab sweeps 10.0; 48x40x56, 150 steps: 1.3
-// and 2.2 ms.
+// one step takes 71 us. 128^3, 200 steps with 2 probes: 8.7 ms, slab sweeps 10.0; 48x40x56, 150 steps:
+// 1.06 (narrow workgroups; 1.28 full) and 2.2 ms.
 #include "fdtd_internal.h"
 #include "tile_queue.h"
 #include "yee_update.h"
@@ -42,12 +42,12 @@ __device__ __forceinline__ float left_of(float x)
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x138, 0xf, 0xf, true));
 }
 
-template <int TS>
-__global__ void __launch_bounds__((64 * adjoint_column_waves(TS)))
+template <int TS, int kNW>
+__global__ void __launch_bounds__(64 * kNW, (kNW != kNarrowWaves ? 1 : adjoint_narrow_pairs(TS) ? 4 : 2))
     k_adj_column(Geom g, ColumnBoxes b, AdjointColumn ac, int kchunk, int ntx, int nty, int ntiles, int cpx)
 {
     typedef float f2 __attribute__((ext_vector_type(2)));
-    constexpr int kNW = adjoint_column_waves(TS), kRows = kNR * kNW;
+    constexpr int kRows = kNR * kNW;
     __shared__ __attribute__((aligned(16))) f2 sE[2][TS][kNW + 1][kCols];  // (Ce lam)_(x, z) of each wave's first row
     __shared__ __attribute__((aligned(16))) f2 sB[TS][kNW + 1][kCols];     // (Ch mu')_(x, z) of wave w - 1's last row
     __shared__ __attribute__((aligned(16))) f2 sF[TS][kNW + 1][kCols];     // h_(x, z) of wave w - 1's last row
@@ -344,15 +344,22 @@ hipError_t launch_ts(const Geom &g, const Fields<float> &src, const Fields<float
                      const AdjointColumn &ac, int zchunk, hipStream_t s)
 {
     const int kchunk = (g.nz + zchunk - 1) / zchunk, nzc = (g.nz + kchunk - 1) / kchunk;
-    int ntx, nty;
-    column_windows(g.nx, g.ny, TS, adjoint_column_waves(TS), &ntx, &nty);
-    const int ntiles = ntx * nty * nzc, nblocks = (ntiles + kXcds - 1) / kXcds * kXcds;
+    constexpr int wide = adjoint_column_waves(TS);
+    const int cpx = cus_per_xcd();
     ColumnBoxes b;
     if (!column_boxes(src, dst, c, &b))
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_adj_column<TS>), dim3(nblocks), dim3(64, adjoint_column_waves(TS)), 0, s, g, b, ac, kchunk,
-                       ntx, nty, ntiles, cus_per_xcd());
-    return hipGetLastError();
+    auto go = [&](auto kernel, int waves) {
+        int ntx, nty;
+        column_windows(g.nx, g.ny, TS, waves, &ntx, &nty);
+        const int ntiles = ntx * nty * nzc, nblocks = (ntiles + kXcds - 1) / kXcds * kXcds;
+        hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(64, waves), 0, s, g, b, ac, kchunk, ntx, nty, ntiles, cpx);
+        return hipGetLastError();
+    };
+    // (as the forward's workgroups)
+    if (column_waves_for(g, TS, wide, adjoint_narrow_pairs(TS), nzc, kXcds * cpx) == kNarrowWaves)
+        return go(k_adj_column<TS, kNarrowWaves>, kNarrowWaves);
+    return go(k_adj_column<TS, wide>, wide);
 }
 
 }  // namespace
