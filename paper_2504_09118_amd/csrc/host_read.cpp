@@ -47,14 +47,18 @@ hipError_t HostReader::begin(int device, hipStream_t s, int n, size_t largest)
 {
     device_ = device;
     stream_ = s;
-    direct_ = closed_ = false;
+    closed_ = false;
     lo_ = hi_ = nullptr;
     pending_ = 0;
     issued_ = taken_ = done_ = 0;
     err_ = hipSuccess;
     const size_t slot = std::min(kSlot, (largest + 4095) / 4096 * 4096);
-    const int slots = (int)std::min<size_t>(kSlots, (size_t)n * ((largest + kSlot - 1) / kSlot));
-    if (slots < 1 || (pinned_ && slot <= slot_ && slots <= slots_))
+    const int slots = (int)std::min<size_t>(kSlots, ((size_t)n * ((largest + kSlot - 1) / kSlot) + 1) / 2);
+    // Making the slots takes 0.1 ms a MiB. An object's first small read goes without them (16^3 read once: 0.15
+    // ms, with slots 0.17 and 0.07 to give them back); from kAtOnce on fresh pages cost the runtime more (64^3:
+    // 1.6 ms, 1.05 with the slots made; 128^3 6.2 and 2.8).
+    const bool worth = reads_++ > 0 || (size_t)n * largest >= kAtOnce;
+    if (slots < 1 || !worth || (pinned_ && slot <= slot_ && slots <= slots_))
         return hipSuccess;
     release();
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;  // another thread's capture is not concerned
@@ -143,8 +147,9 @@ hipError_t HostReader::add(void *dst, const void *dev, size_t bytes)
     hi_ = lo_ ? std::max(hi_, d + bytes) : d + bytes;
     lo_ = lo_ ? std::min(lo_, d) : d;
     if (!pinned_ || known_to_runtime(dst)) {
-        direct_ = true;
-        const hipError_t e = hipMemcpyAsync(dst, dev, bytes, hipMemcpyDeviceToHost, stream_);
+        hipError_t e = hipMemcpyAsync(dst, dev, bytes, hipMemcpyDeviceToHost, stream_);
+        if (e == hipSuccess)  // (pageable copies left to queue up: 1.6 ms for 64^3, waited for one by one 0.5)
+            e = hipStreamSynchronize(stream_);
         return err_ == hipSuccess ? err_ = e : err_;
     }
     const size_t n = (bytes + slot_ - 1) / slot_, len = std::min(slot_, ((bytes + n - 1) / n + 4095) / 4096 * 4096);
@@ -187,11 +192,8 @@ hipError_t HostReader::finish()
     cv_.wait(lk, [&] { return done_ == issued_; });
     lk.unlock();
     for (; nthreads_ > 0; --nthreads_) thread_[nthreads_ - 1].join();
-    if (direct_ || err_ != hipSuccess) {
-        const hipError_t e = hipStreamSynchronize(stream_);
-        if (err_ == hipSuccess)
-            err_ = e;
-    }
+    if (err_ != hipSuccess)
+        (void)hipStreamSynchronize(stream_);  // nothing enqueued here outlives the call
     return err_;
 }
 

@@ -37,6 +37,8 @@ private:
     static constexpr int kSlots = 8, kThreads = 6;
     static constexpr size_t kPerThread = 2 << 20;  // a thread costs about 20 us to start, 2 MiB 140 to copy
 
+    static constexpr size_t kAtOnce = 512 << 10;
+
     struct Part {
         char *dst;
         size_t bytes;
@@ -49,11 +51,11 @@ private:
     char *pinned_ = nullptr;
     size_t slot_ = 0;
     int slots_ = 0, events_ = 0;
+    long long reads_ = 0;
     hipEvent_t ev_[kSlots] = {};
 
     int device_ = 0;
     hipStream_t stream_ = nullptr;
-    bool direct_ = false;
     char *lo_ = nullptr, *hi_ = nullptr;  // hull of the destinations of this read
     size_t pending_ = 0;                  // bytes in slots that no thread has taken
     std::mutex mu_;
