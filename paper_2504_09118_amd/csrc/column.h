@@ -482,7 +482,7 @@ __device__ __forceinline__ void column_tile(const Geom &g, const Boxes &b, int k
 // One workgroup per tile (queue null, in the order remap names), or one workgroup per CU taking tiles
 // from the queue.
 template <typename S, int TS, bool CE_ARR, bool CH_ARR, int kNW>
-__global__ void __launch_bounds__(64 * kNW, (kNW != kNarrowWaves ? 1 : column_narrow_pairs(TS, CE_ARR, CH_ARR) ? 4 : 2))
+__global__ void __launch_bounds__(64 * kNW, (kNW != kNarrowWaves ? 1 : column_narrow_pairs(sizeof(S) == 2, TS, CE_ARR, CH_ARR) ? 4 : 2))
     k_column(Geom g, FieldBoxes<S> b, int kchunk, int ntx, int nty, int ntiles, int nvb, int remap, int cpx,
              unsigned *queue)
 {
@@ -534,9 +534,9 @@ hipError_t launch_column(const Geom &g, const Fields<S> &src, const Fields<S> &d
     auto pick = [&](auto ce, auto ch) {
         constexpr bool CE = decltype(ce)::value, CH = decltype(ch)::value;
         constexpr int wide = column_waves<S, TS, CE, CH>();
-        if constexpr (column_has_narrow(sizeof(S) == 2))
-            if (column_waves_for(g, TS, wide, column_narrow_pairs(TS, CE, CH), nzc, kXcds * cpx) == kNarrowWaves)
-                return go(k_column<S, TS, CE, CH, kNarrowWaves>, kNarrowWaves);
+        const bool pairs = column_narrow_pairs(sizeof(S) == 2, TS, CE, CH);
+        if (column_waves_for(g, TS, wide, pairs, nzc, kXcds * cpx) == kNarrowWaves)
+            return go(k_column<S, TS, CE, CH, kNarrowWaves>, kNarrowWaves);
         return go(k_column<S, TS, CE, CH, wide>, wide);
     };
     using yes = std::true_type;

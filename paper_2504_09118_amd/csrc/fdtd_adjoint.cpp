@@ -615,11 +615,11 @@ int fdtd_adjoint_create(fdtd_t s, const fdtd_adjoint_problem *p, fdtd_adjoint_t 
         }
     }
     for (int ts = 1; ts <= 4; ++ts) {
-        a->zs_fwd[ts] = fdtd::column_zsplit(g, ts, fdtd::driven_waves_of(ts, s->ch_arr), true,
-                                           fdtd::driven_narrow_pairs(ts), s->device);
+        a->zs_fwd[ts] = fdtd::column_zsplit(g, ts, fdtd::driven_waves_of(ts, s->ch_arr), fdtd::driven_narrow_pairs(ts),
+                                           s->device);
         if (ts <= 2)
-            a->zs_rev[ts] = fdtd::column_zsplit(g, ts, fdtd::adjoint_column_waves(ts), true,
-                                               fdtd::adjoint_narrow_pairs(ts), s->device);
+            a->zs_rev[ts] = fdtd::column_zsplit(g, ts, fdtd::adjoint_column_waves(ts), fdtd::adjoint_narrow_pairs(ts),
+                                               s->device);
     }
     // A tile of a four-step sweep marches its planes and 7 more. Where tiles own three planes or fewer, two
     // sweeps of two steps cost less or the same (48x40x56: 4.9 us per step, not 5.6; 64^3: 5.7, not 6.3; 96^3:

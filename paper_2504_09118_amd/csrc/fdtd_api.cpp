@@ -500,7 +500,7 @@ int best_zsplit(long long tiles, int nz, int redo, int min_planes, int cus, int 
 }  // namespace
 
 namespace fdtd {
-int column_zsplit(const Geom &g, int ts, int wide, bool narrow, bool pairs, int device)
+int column_zsplit(const Geom &g, int ts, int wide, bool pairs, int device)
 {
     const int cus = device_cus(device);
     double best = -1.0;
@@ -508,9 +508,8 @@ int column_zsplit(const Geom &g, int ts, int wide, bool narrow, bool pairs, int 
     for (int zc = 1; zc <= g.nz; ++zc) {
         if ((g.nz + zc - 1) / zc > kTemporalMaxChunk && zc < g.nz)
             continue;
-        double cost = column_cost(g, ts, wide, pairs, zc, cus);
-        if (narrow)
-            cost = std::min(cost, column_cost(g, ts, kNarrowWaves, pairs, zc, cus));
+        const double cost =
+            std::min(column_cost(g, ts, wide, pairs, zc, cus), column_cost(g, ts, kNarrowWaves, pairs, zc, cus));
         if (best < 0 || cost < best) {
             best = cost;
             zc_best = zc;
@@ -700,8 +699,7 @@ int fdtd_create(int nx, int ny, int nz, double dx, double dt, const fdtd_coef *c
         if (h->tvariant == 0 && !h->nt_stores) {
             const bool half = is16(h->storage), ce = h->ce_arr, ch = h->ch_arr;
             h->tz_own[ts] = fdtd::column_zsplit(p.g, ts, fdtd::column_waves_of(half, ts, ce, ch),
-                                                fdtd::column_has_narrow(half), fdtd::column_narrow_pairs(ts, ce, ch),
-                                                o->device);
+                                                fdtd::column_narrow_pairs(half, ts, ce, ch), o->device);
         } else {
             const int tv = ts > 3 ? 0 : h->tvariant;
             const int own = fdtd::temporal_own_rows(ts, tv), w = fdtd::temporal_width(tv);

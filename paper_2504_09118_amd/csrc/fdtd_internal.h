@@ -142,14 +142,16 @@ inline void column_windows(int nx, int ny, int ts, int waves, int *ntx, int *nty
     *ntx = nx <= 64 ? 1 : (nx - 2 * ts + sw - 1) / sw;
     *nty = ny <= kColumnRows * waves ? 1 : (ny - 2 * ts + sr - 1) / sr;
 }
-// A cavity too small to give every CU a full workgroup takes workgroups of 8 waves (FP32): a plane's chain of
+// A cavity too small to give every CU a full workgroup takes workgroups of 8 waves: a plane's chain of
 // stages and barriers is shorter with two waves per SIMD than with four. Per plane of a full workgroup,
 // measured: 0.7 with a workgroup per CU, 0.9 with two (32^3, 4 steps: 19.7 us, narrow 14.0; 64^3 22.5 and
 // 17.4; at 128^3, where the wide windows fill the chip, 43 and 50).
 constexpr int kNarrowWaves = 8;
-constexpr bool column_has_narrow(bool half) { return !half; }
 // Whether two narrow workgroups fit a CU's registers.
-constexpr bool column_narrow_pairs(int ts, bool ce_arr, bool ch_arr) { return !(ts > 2 && ce_arr && ch_arr); }
+constexpr bool column_narrow_pairs(bool half, int ts, bool ce_arr, bool ch_arr)
+{
+    return half ? !(ts > 2 || (ts > 1 && ce_arr && ch_arr)) : !(ts > 2 && ce_arr && ch_arr);
+}
 // Time of a sweep in planes of a full workgroup.
 inline double column_cost(const Geom &g, int ts, int waves, bool pairs, int zchunk, int cus)
 {

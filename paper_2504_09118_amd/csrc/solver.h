@@ -49,9 +49,8 @@ int solver_check(fdtd_t h);
 // Mark the solver failed after a device error and set the message.
 int solver_device_fail(fdtd_t h, hipError_t e, const char *what);
 
-// z-split of a column sweep of ts steps with this many waves a workgroup; narrow: or kNarrowWaves, two
-// workgroups a CU with pairs.
-int column_zsplit(const Geom &g, int ts, int wide, bool narrow, bool pairs, int device);
+// z-split of a column sweep of ts steps with wide waves a workgroup or kNarrowWaves, with pairs two of those a CU.
+int column_zsplit(const Geom &g, int ts, int wide, bool pairs, int device);
 
 // fdtd_step with the temporal sweeps' scheduling counters (kSchedWords words, zero
 // before and after each launch) taken from queue instead of the solver's arena.

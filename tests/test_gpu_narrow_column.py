@@ -41,3 +41,29 @@ def test_narrow_windows_same_bits(shape, medium):
                 got = s.get_fields(dtype=np.float32)
                 for name, a, b in zip(("Ex", "Ey", "Ez", "Hx", "Hy", "Hz"), got, want):
                     assert np.array_equal(a, b), f"tb {tb} zchunks {zc}: {name}"
+
+
+@pytest.mark.parametrize("storage", ["f16", "bf16", "f16c", "bf16c"])
+@pytest.mark.parametrize("shape", [(64, 17, 7), (12, 25, 33), (121, 15, 20), (2, 2, 2)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_narrow_windows_16bit_equal_the_streaming_form(shape, storage, monkeypatch):
+    """16-bit storage rounds once a sweep, as the form that large states take (FDTD_NT_STORES = 1): equal."""
+    import paper_2504_09118_amd as P
+
+    nx, ny, nz = shape
+    eps = ci.uniform_cell_eps(nx, ny, nz, seed=4, lo=1.0, hi=4.0)
+    mu = ci.uniform_cell_eps(nx, ny, nz, seed=5, lo=1.0, hi=2.0)
+    for e, m in ((None, None), (eps, None), (eps, mu)):
+        for tb in (1, 2, 3, 4):
+            outs = []
+            for pol, splits in (("1", [None]), ("0", [None, 1, nz])):
+                monkeypatch.setenv("FDTD_NT_STORES", pol)
+                with P.Solver(nx, ny, nz, eps_r=e, mu_r=m, storage=storage, tb_steps=tb) as s:
+                    for zc in splits:
+                        if zc:
+                            s.set_schedule("temporal", tb, 0, zc)
+                        s.init_random(12)
+                        s.step(2 * tb + 1)
+                        outs.append(s.get_fields(dtype=np.float32))
+            for got in outs[1:]:
+                assert all(np.array_equal(a, b) for a, b in zip(got, outs[0])), f"tb {tb}"
