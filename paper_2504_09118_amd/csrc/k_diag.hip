@@ -34,9 +34,8 @@ __device__ __forceinline__ bool h_normal(int f, int i, int j, int k, int nx, int
 }
 
 template <typename T>
-__device__ __forceinline__ double coef_at(const T *arr, T s, bool zero, long long o)
+__device__ __forceinline__ double coef_at(const T *arr, T s, long long o)
 {
-    if (zero) return 0.0;
     return arr ? (double)arr[o] : (double)s;
 }
 
@@ -64,9 +63,11 @@ __device__ __forceinline__ void reduce(double (*red)[kBlock], const double *v)
 }
 
 // Workgroup b walks the runs b, b + kGrid, ... of kBlock nodes within a plane (the index of a run is
-// uniform, a node's row comes from a multiplication). What bounds it is the FP64 divisions (twelve a
-// node). A second small kernel adds up the partial results: doing that in the workgroup that finishes
-// last needs a fence in each of the 1024, and took 92 us against 28 for both kernels on 133 x 40 x 71.
+// uniform, a node's row comes from a multiplication). What bounds it: the latency of a run's loads, which
+// are all in flight at once, and twelve FP64 divisions a node. 133 x 40 x 71, both media: 11.5 us, 22.4 with
+// each load behind the test that needs it; 256^3 with the second kernel and the copy 291 us, 685 before. A
+// second small kernel adds up the partial results: doing that in the workgroup that finishes last needs a
+// fence in each of the 1024, and took 92 us when the two kernels took 28.
 template <typename T>
 __global__ void __launch_bounds__(kBlock)
     k_diag(Geom g, PlaneIndex ix, Fields<T> f, Coefs<typename Store<T>::C> c, double *partial)
@@ -86,55 +87,62 @@ __global__ void __launch_bounds__(kBlock)
             continue;
         const int j = (int)ix.row(q0, X, nx), i = (int)q0 - j * X;
         const long long o = g.at(i, j, k);
-        int ex[6];
+        // every value that the node may need, before the first that depends on one: a load behind each of
+        // the tests below is a memory latency of its own (at a far wall a neighbour is the node itself)
+        const long long ox = o + (i < nx), oy = o + (j < ny ? px : 0), oz = o + (k < nz ? P : 0);
+        double v[6], ce[3], ch[3], chn[3];
+#pragma unroll
+        for (int q = 0; q < 6; ++q) v[q] = val(f.f[q], o, g.lo_rec(q));
+        const double exy = val(f.f[0], oy, g.lo_rec(0)), exz = val(f.f[0], oz, g.lo_rec(0)),
+                     eyx = val(f.f[1], ox, g.lo_rec(1)), eyz = val(f.f[1], oz, g.lo_rec(1)),
+                     ezx = val(f.f[2], ox, g.lo_rec(2)), ezy = val(f.f[2], oy, g.lo_rec(2));
+        const double hn1[3] = {val(f.f[3], ox, g.lo_rec(3)), val(f.f[4], oy, g.lo_rec(4)),
+                               val(f.f[5], oz, g.lo_rec(5))};
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            ce[q] = coef_at(c.ce[q], c.ce_s, o);
+            ch[q] = coef_at(c.ch[q], c.ch_s, o);
+            chn[q] = coef_at(c.ch[q], c.ch_s, q == 0 ? ox : q == 1 ? oy : oz);
+        }
+        bool ex[6];
+#pragma unroll
         for (int q = 0; q < 6; ++q) {
             int a, b, d;
             extents(g, q, a, b, d);
             ex[q] = i < a && j < b && k < d;
         }
+#pragma unroll
         for (int q = 0; q < 3; ++q) {
             if (!ex[q]) continue;
-            double e = val(f.f[q], o, g.lo_rec(q));
+            const double e = v[q];
             if (!isfinite(e)) bad += 1;
             se += e * e;
             const bool wall = e_tan(q, i, j, k, nx, ny, nz);
             if (wall) {
                 mtan = fmax(mtan, fabs(e));
-            } else {
-                const double ce = coef_at(c.ce[q], c.ce_s, false, o);
-                if (ce != 0.0) w += e * e / ce;
+            } else if (ce[q] != 0.0) {
+                w += e * e / ce[q];
             }
         }
-        const double Ex0 = ex[0] ? val(f.f[0], o, g.lo_rec(0)) : 0.0, Ey0 = ex[1] ? val(f.f[1], o, g.lo_rec(1)) : 0.0,
-                     Ez0 = ex[2] ? val(f.f[2], o, g.lo_rec(2)) : 0.0;
+        const double Ex0 = ex[0] ? v[0] : 0.0, Ey0 = ex[1] ? v[1] : 0.0, Ez0 = ex[2] ? v[2] : 0.0;
+        const double curl[3] = {(eyz - Ey0) - (ezy - Ez0), (ezx - Ez0) - (exz - Ex0), (exy - Ex0) - (eyx - Ey0)};
+#pragma unroll
         for (int q = 3; q < 6; ++q) {
             if (!ex[q]) continue;
-            double h = val(f.f[q], o, g.lo_rec(q));
+            const double h = v[q];
             if (!isfinite(h)) bad += 1;
             sh += h * h;
             if (h_normal(q, i, j, k, nx, ny, nz)) continue;
-            const double ch = coef_at(c.ch[q - 3], c.ch_s, false, o);
-            if (ch == 0.0) continue;
-            double d;
-            if (q == 3)
-                d = (val(f.f[1], o + P, g.lo_rec(1)) - Ey0) - (val(f.f[2], o + px, g.lo_rec(2)) - Ez0);
-            else if (q == 4)
-                d = (val(f.f[2], o + 1, g.lo_rec(2)) - Ez0) - (val(f.f[0], o + P, g.lo_rec(0)) - Ex0);
-            else
-                d = (val(f.f[0], o + px, g.lo_rec(0)) - Ex0) - (val(f.f[1], o + 1, g.lo_rec(1)) - Ey0);
-            const double hn = h + ch * d;
-            w += h * hn / ch;
+            if (ch[q - 3] == 0.0) continue;
+            const double hn = h + ch[q - 3] * curl[q - 3];
+            w += h * hn / ch[q - 3];
         }
         if (i < nx && j < ny && k < nz) {
             // B = H/Ch, taken as 0 on wall-normal nodes (constant in time)
-            auto b = [&](int q, int ii, int jj, int kk) -> double {
-                if (h_normal(q, ii, jj, kk, nx, ny, nz)) return 0.0;
-                const long long oo = g.at(ii, jj, kk);
-                const double ch = coef_at(c.ch[q - 3], c.ch_s, false, oo);
-                return ch != 0.0 ? val(f.f[q], oo, g.lo_rec(q)) / ch : 0.0;
-            };
-            const double dv = (b(3, i + 1, j, k) - b(3, i, j, k)) + (b(4, i, j + 1, k) - b(4, i, j, k)) +
-                              (b(5, i, j, k + 1) - b(5, i, j, k));
+            auto b = [&](bool normal, double h, double coef) { return !normal && coef != 0.0 ? h / coef : 0.0; };
+            const double dv = (b(i + 1 == nx, hn1[0], chn[0]) - b(i == 0, v[3], ch[0])) +
+                              (b(j + 1 == ny, hn1[1], chn[1]) - b(j == 0, v[4], ch[1])) +
+                              (b(k + 1 == nz, hn1[2], chn[2]) - b(k == 0, v[5], ch[2]));
             mdiv = fmax(mdiv, fabs(dv));
         }
     }
