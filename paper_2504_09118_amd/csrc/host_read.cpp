@@ -52,14 +52,18 @@ hipError_t HostReader::begin(int device, hipStream_t s, int n, size_t largest)
     pending_ = 0;
     issued_ = taken_ = done_ = 0;
     err_ = hipSuccess;
-    const size_t slot = std::min(kSlot, (largest + 4095) / 4096 * 4096);
-    const int slots = (int)std::min<size_t>(kSlots, ((size_t)n * ((largest + kSlot - 1) / kSlot) + 1) / 2);
-    // Making the slots takes 0.1 ms a MiB. An object's first small read goes without them (16^3 read once: 0.15
-    // ms, with slots 0.17 and 0.07 to give them back); from kAtOnce on fresh pages cost the runtime more (64^3:
-    // 1.6 ms, 1.05 with the slots made; 128^3 6.2 and 2.8).
-    const bool worth = reads_++ > 0 || (size_t)n * largest >= kAtOnce;
-    if (slots < 1 || !worth || (pinned_ && slot <= slot_ && slots <= slots_))
+    size_t slot = std::min(kSlot, (largest + 4095) / 4096 * 4096);
+    int slots = (int)std::min<size_t>(kSlots, ((size_t)n * ((largest + kSlot - 1) / kSlot) + 1) / 2);
+    // Making the slots takes about a millisecond, so they wait until an object has read kWorth (two fields of
+    // 3 MiB fetched once: 0.4 ms, 1.5 with the slots made). One array alone is worth a slot (0.9 MiB in fresh
+    // pages: 0.5 ms by the runtime, 0.2).
+    read_ += (size_t)n * largest;
+    if (slots < 1 || (n > 1 && read_ < kWorth) || (pinned_ && slot <= slot_ && slots <= slots_))
         return hipSuccess;
+    if (pinned_) {  // a larger read than the last: once more only
+        slot = kSlot;
+        slots = kSlots;
+    }
     release();
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;  // another thread's capture is not concerned
     (void)hipThreadExchangeStreamCaptureMode(&mode);

@@ -32,12 +32,12 @@ public:
 
 private:
     // a copy and its event cost about 15 us beside the bytes: 256^3 FP32 fields (404 MB) arrive in 19 ms with
-    // 512 KiB slots, 11 with 2 MiB; 31 ms by one thread, 12 by four
+    // 512 KiB slots, 11 with 2 MiB; 31 ms by one thread, 12 by four, 11 by six
     static constexpr size_t kSlot = 2 << 20;
-    static constexpr int kSlots = 8, kThreads = 6;
+    static constexpr int kSlots = 8, kThreads = 4;
     static constexpr size_t kPerThread = 2 << 20;  // a thread costs about 20 us to start, 2 MiB 140 to copy
 
-    static constexpr size_t kAtOnce = 512 << 10;
+    static constexpr size_t kWorth = 16 << 20;
 
     struct Part {
         char *dst;
@@ -51,7 +51,7 @@ private:
     char *pinned_ = nullptr;
     size_t slot_ = 0;
     int slots_ = 0, events_ = 0;
-    long long reads_ = 0;
+    size_t read_ = 0;  // bytes read so far
     hipEvent_t ev_[kSlots] = {};
 
     int device_ = 0;
