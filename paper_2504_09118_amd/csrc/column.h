@@ -112,6 +112,7 @@ __device__ __forceinline__ void column_tile(const Geom &g, const Boxes &b, int k
     const int i = tile_x * (kCols - 2 * TS) + lane;
     const int row0 = wave * kNR, j0 = tile_y * (kRows - 2 * TS) + row0;  // first row of the wave
     const bool col_own = i < nx && (lane >= TS || tile_x == 0) && (lane < kCols - TS || tile_x == ntx - 1);
+    const bool wall_x = i < 1 || i >= nx;
 
     // the rows beside the window, which its outermost rows read: never written
     if (wave == 0) {
@@ -318,18 +319,33 @@ __device__ __forceinline__ void column_tile(const Geom &g, const Boxes &b, int k
                     const auto &Cs = RC[HS(sp, ph)];
                     if (livep) {
                         const f2 dn = sH[sp][wave][lane];  // (Hx, Hz) of row j0 - 1
+                        int jv = j0;
+                        if constexpr (Drive::on)
+                            __asm__ volatile("" : "+s"(jv));
                         __builtin_amdgcn_sched_barrier(0);
                         // the row next to another wave's comes last, and of it the parts that read dn
 #pragma unroll
                         for (int r = kNR - 1; r >= 0; --r) {
-                            const float ey =
-                                curl_update(E[1][r], Cs[1][r], Hn[0][r], Hd[0][r], Hn[2][r], left_of(Hn[2][r]));
+                            float cy = (Hn[0][r] - Hd[0][r]) - (Hn[2][r] - left_of(Hn[2][r]));
+                            // Driven: walls and outside take no curl, for 0 * curl is NaN where a curl is not
+                            // finite, and the forward's state is that of single slab sweeps (2 to 3 % of a
+                            // sweep; by rows from scalars, or the masks are spilled: 5 %). Rows and columns
+                            // beyond the wall follow: their H stays 0.
+                            if constexpr (Drive::on)
+                                cy = pp >= 1 && !wall_x ? cy : 0.0f;
+                            const float ey = __builtin_fmaf(Cs[1][r], cy, E[1][r]);
                             const float hyl = Hn[1][r] - left_of(Hn[1][r]), hyd = Hn[1][r] - Hd[1][r];
                             if (r == 0)
                                 __builtin_amdgcn_sched_barrier(0);
                             const float hxj = r > 0 ? Hn[0][r - 1] : dn.x, hzj = r > 0 ? Hn[2][r - 1] : dn.y;
-                            const float ex = __builtin_fmaf(Cs[0][r], (Hn[2][r] - hzj) - hyd, E[0][r]);
-                            const float ez = __builtin_fmaf(Cs[2][r], hyl - (Hn[0][r] - hxj), E[2][r]);
+                            float cx = (Hn[2][r] - hzj) - hyd, cz = hyl - (Hn[0][r] - hxj);
+                            if constexpr (Drive::on) {
+                                const bool jw = jv + r >= 1 && jv + r < ny;
+                                cx = jw && pp >= 1 ? cx : 0.0f;
+                                cz = jw && !wall_x ? cz : 0.0f;
+                            }
+                            const float ex = __builtin_fmaf(Cs[0][r], cx, E[0][r]);
+                            const float ez = __builtin_fmaf(Cs[2][r], cz, E[2][r]);
                             if (CE_ARR) {
                                 // coefficients are 0 on the walls and outside: E + 0 * curl = E
                                 E[0][r] = ex;
