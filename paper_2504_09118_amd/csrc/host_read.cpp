@@ -136,9 +136,9 @@ void HostReader::spawn(std::unique_lock<std::mutex> &lk)
 
 hipError_t HostReader::add(void *dst, const void *dev, size_t bytes)
 {
+    std::unique_lock<std::mutex> lk(mu_);  // (a worker of an earlier array may be writing err_)
     if (err_ != hipSuccess || bytes == 0)
         return err_;
-    std::unique_lock<std::mutex> lk(mu_);
     char *d = (char *)dst;
     if (lo_ && d < hi_ && d + bytes > lo_) {  // arrays that may overlap arrive in order
         while (taken_ < issued_) {
