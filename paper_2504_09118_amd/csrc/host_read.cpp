@@ -31,10 +31,18 @@ bool known_to_runtime(const void *p)
     return at.type == hipMemoryTypeHost || at.type == hipMemoryTypeManaged || at.type == hipMemoryTypeDevice;
 }
 
+// Pinned memory is made and freed in the relaxed mode: another thread's capture is not concerned.
+struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
 }  // namespace
 
 void HostReader::release()
 {
+    RelaxedCapture relaxed;
     for (int q = 0; q < events_; ++q) (void)hipEventDestroy(ev_[q]);
     events_ = 0;
     if (pinned_)
@@ -65,10 +73,8 @@ hipError_t HostReader::begin(int device, hipStream_t s, int n, size_t largest)
         slots = kSlots;
     }
     release();
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;  // another thread's capture is not concerned
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    RelaxedCapture relaxed;
     const hipError_t got = hipHostMalloc((void **)&pinned_, slot * slots, hipHostMallocDefault);
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
     if (got != hipSuccess) {
         (void)hipGetLastError();
         pinned_ = nullptr;  // every array is copied by the runtime

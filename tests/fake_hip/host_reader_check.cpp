@@ -43,12 +43,34 @@ static void error_of_a_worker()
     fake::on_sync = [] { return hipSuccess; };
 }
 
+// Making and freeing pinned memory leaves another thread's capture alone, also where larger slots take the
+// place of smaller ones.
+static void capture_mode()
+{
+    std::vector<char> dev(6 * MiB, 1), dst(6 * MiB);
+    fake::Stream s;
+    {
+        HostReader r;
+        for (size_t n : {MiB, 6 * MiB}) {
+            CHECK(r.begin(0, &s, 1, n) == hipSuccess);
+            CHECK(r.add(dst.data(), dev.data(), n) == hipSuccess);
+            CHECK(r.finish() == hipSuccess);
+        }
+        CHECK(fake::allocations >= 1);
+        CHECK(memcmp(dst.data(), dev.data(), 6 * MiB) == 0);
+    }
+    CHECK(fake::unrelaxed == 0);
+    CHECK(fake::mode == hipStreamCaptureModeGlobal);
+}
+
 int main(int argc, char **argv)
 {
     for (int a = 1; a < argc; ++a) {
         const std::string what = argv[a];
         if (what == "error_of_a_worker")
             error_of_a_worker();
+        else if (what == "capture_mode")
+            capture_mode();
         else
             CHECK(!"known check");
     }

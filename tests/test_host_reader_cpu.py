@@ -34,5 +34,6 @@ def check(tmp_path_factory):
     return run
 
 
-def test_error_of_a_worker(check):
-    check("error_of_a_worker")
+@pytest.mark.parametrize("name", ["error_of_a_worker", "capture_mode"])
+def test_reader(check, name):
+    check(name)
