@@ -442,8 +442,7 @@ int backward_impl(fdtd_adjoint_t a, double *grad, void *const lam0[3], int lam0_
         bytes[1 + q] = (size_t)X * Y * Z * (lam0_dtype == FDTD_F64 ? sizeof(double) : sizeof(float));
     }
     fdtd::HostReader &reader = s->reader;
-    if (e == hipSuccess)
-        e = reader.begin(s->device, s->stream, lam0 ? 4 : 1, *std::max_element(bytes, bytes + 4));
+    reader.begin(s->device, s->stream, lam0 ? 4 : 1, *std::max_element(bytes, bytes + 4));
     if (e == hipSuccess)
         e = reader.add(grad, a->d_grad, bytes[0]);
     for (int q = 0; q < 3 && lam0 && e == hipSuccess; ++q) {

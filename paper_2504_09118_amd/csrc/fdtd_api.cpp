@@ -380,7 +380,9 @@ hipError_t unpack_all(fdtd_t h, void *const dst[6], bool staged, void *const *bo
         fdtd::extents(h->plan.g, f, X, Y, Z);
         bytes[f] = (size_t)X * Y * Z * sizeof(S);
     }
-    hipError_t e = staged ? h->reader.begin(h->device, h->stream, 6, *std::max_element(bytes, bytes + 6)) : hipSuccess;
+    hipError_t e = hipSuccess;
+    if (staged)
+        h->reader.begin(h->device, h->stream, 6, *std::max_element(bytes, bytes + 6));
     for (int f = 0; f < 6 && e == hipSuccess; ++f) {
         e = boxes[f] ? fdtd::launch_unpack<T, S>(h->plan.g, f, 1, src, out, h->stream, scale)
                      : hipMemsetAsync(out[f], 0, bytes[f], h->stream);

@@ -566,7 +566,8 @@ hipError_t fetch_fields(fdtd_pool_t p, Req &r, void *const host[6])
     }
     S *out[6];
     for (int q = 0; q < 6; ++q) out[q] = (S *)r.staging;
-    hipError_t e = p->reader.begin(p->device, p->fetch_stream, 6, *std::max_element(bytes, bytes + 6));
+    hipError_t e = hipSuccess;
+    p->reader.begin(p->device, p->fetch_stream, 6, *std::max_element(bytes, bytes + 6));
     for (int f = 0; f < 6 && e == hipSuccess; ++f) {
         e = fdtd::launch_unpack<float, S>(r.plan.g, f, 1, r.fld[r.cur], out, p->fetch_stream);
         if (e == hipSuccess)

@@ -5,6 +5,7 @@
 #include <algorithm>
 #include <cstdint>
 #include <cstring>
+#include <new>
 
 namespace fdtd {
 namespace {
@@ -38,70 +39,138 @@ struct RelaxedCapture {
     ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
 };
 
-}  // namespace
+// What the readers of a device share. Nothing is freed when the process ends: the runtime may be gone by then.
+struct Shared {
+    size_t read = 0;  // bytes read so far
+    int sets = 0;     // made and not freed, leased ones among them
+    PinnedSlots *idle[kSlotSets] = {};
+    int nidle = 0;
+};
+constexpr size_t kWorth = 32 << 20, kLeast = 4 << 20, kLeastOne = 512 << 10;
+constexpr int kDevices = 64;
+Shared g_shared[kDevices];
+std::mutex g_mu;
+int g_readers = 0;  // objects
 
-void HostReader::release()
+void destroy(PinnedSlots *p)
 {
     RelaxedCapture relaxed;
-    for (int q = 0; q < events_; ++q) (void)hipEventDestroy(ev_[q]);
-    events_ = 0;
-    if (pinned_)
-        (void)hipHostFree(pinned_);
-    pinned_ = nullptr;
-    slots_ = 0;
+    for (hipEvent_t e : p->ev)
+        if (e)
+            (void)hipEventDestroy(e);
+    if (p->mem)
+        (void)hipHostFree(p->mem);
+    delete p;
 }
 
-hipError_t HostReader::begin(int device, hipStream_t s, int n, size_t largest)
+PinnedSlots *create(size_t slot, int slots)
+{
+    RelaxedCapture relaxed;
+    auto *p = new (std::nothrow) PinnedSlots{nullptr, slot, slots, {}};
+    if (!p)
+        return nullptr;
+    hipError_t e = hipHostMalloc((void **)&p->mem, slot * slots, hipHostMallocDefault);
+    if (e != hipSuccess)
+        p->mem = nullptr;
+    for (int q = 0; q < slots && e == hipSuccess; ++q) e = hipEventCreateWithFlags(&p->ev[q], hipEventDisableTiming);
+    if (e == hipSuccess)
+        return p;
+    (void)hipGetLastError();
+    destroy(p);
+    return nullptr;
+}
+
+// Slots for a read of n arrays of at most largest bytes, or null: the runtime copies. Making them takes one
+// to two milliseconds and saves 27 us for a MiB in mapped pages, more in fresh ones, so the first set waits
+// until kWorth has been read, the next ones (readers at the same time) for as much each. One array alone is
+// worth a set of its size at once (0.9 MiB in fresh pages: 0.5 ms by the runtime, 0.2).
+PinnedSlots *lease(int device, int n, size_t largest)
+{
+    size_t slot = std::min(kSlot, (largest + 4095) / 4096 * 4096);
+    int slots = (int)std::min<size_t>(kSlots, ((size_t)n * ((largest + kSlot - 1) / kSlot) + 1) / 2);
+    if (slots < 1 || device < 0 || device >= kDevices)
+        return nullptr;
+    Shared &d = g_shared[device];
+    PinnedSlots *small = nullptr;
+    {
+        std::lock_guard<std::mutex> lk(g_mu);
+        for (int q = d.nidle - 1; q >= 0; --q) {
+            PinnedSlots *p = d.idle[q];
+            if (p->slot >= slot && p->slots >= slots) {
+                d.idle[q] = d.idle[--d.nidle];
+                return p;
+            }
+        }
+        const bool worth = d.read >= kWorth;
+        if (d.nidle > 0 && (worth || n == 1)) {  // too small for this read: once more only
+            small = d.idle[--d.nidle];
+        } else if (d.sets < kSlotSets && (d.read >= kWorth * (d.sets + 1) || n == 1)) {
+            ++d.sets;
+        } else {
+            return nullptr;
+        }
+        if (small || worth) {
+            slot = kSlot;
+            slots = kSlots;
+        }
+    }
+    if (small)
+        destroy(small);
+    PinnedSlots *p = create(slot, slots);
+    if (!p) {
+        std::lock_guard<std::mutex> lk(g_mu);
+        --d.sets;
+    }
+    return p;
+}
+
+}  // namespace
+
+HostReader::HostReader()
+{
+    std::lock_guard<std::mutex> lk(g_mu);
+    ++g_readers;
+}
+
+// The last object leaves one set to the next.
+HostReader::~HostReader()
+{
+    std::lock_guard<std::mutex> lk(g_mu);
+    if (--g_readers > 0)
+        return;
+    for (Shared &d : g_shared)
+        for (; d.nidle > 1; --d.sets) destroy(d.idle[--d.nidle]);
+}
+
+void HostReader::begin(int device, hipStream_t s, int n, size_t largest)
 {
     device_ = device;
     stream_ = s;
+    n_ = n;
+    largest_ = largest;
+    slots_ = nullptr;
+    // a small read is left to the runtime: a solver that read 1.7 MB in slots ends 50 us later, all it gained
+    tried_ = (size_t)n * largest < (n == 1 ? kLeastOne : kLeast);
     closed_ = false;
     lo_ = hi_ = nullptr;
     pending_ = 0;
     issued_ = taken_ = done_ = 0;
     err_ = hipSuccess;
-    size_t slot = std::min(kSlot, (largest + 4095) / 4096 * 4096);
-    int slots = (int)std::min<size_t>(kSlots, ((size_t)n * ((largest + kSlot - 1) / kSlot) + 1) / 2);
-    // Making the slots takes about a millisecond, so they wait until an object has read kWorth (two fields of
-    // 3 MiB fetched once: 0.4 ms, 1.5 with the slots made). One array alone is worth a slot (0.9 MiB in fresh
-    // pages: 0.5 ms by the runtime, 0.2).
-    read_ += (size_t)n * largest;
-    if (slots < 1 || (n > 1 && read_ < kWorth) || (pinned_ && slot <= slot_ && slots <= slots_))
-        return hipSuccess;
-    if (pinned_) {  // a larger read than the last: once more only
-        slot = kSlot;
-        slots = kSlots;
-    }
-    release();
-    RelaxedCapture relaxed;
-    const hipError_t got = hipHostMalloc((void **)&pinned_, slot * slots, hipHostMallocDefault);
-    if (got != hipSuccess) {
-        (void)hipGetLastError();
-        pinned_ = nullptr;  // every array is copied by the runtime
-        return hipSuccess;
-    }
-    for (; events_ < slots; ++events_) {
-        const hipError_t e = hipEventCreateWithFlags(&ev_[events_], hipEventDisableTiming);
-        if (e != hipSuccess) {
-            release();
-            return e;
-        }
-    }
-    slot_ = slot;
-    slots_ = slots;
-    return hipSuccess;
+    std::lock_guard<std::mutex> lk(g_mu);
+    if (device >= 0 && device < kDevices)
+        g_shared[device].read += (size_t)n * largest;
 }
 
 // Take the next filled slot and copy it out (lk held on entry and on return).
 void HostReader::take(std::unique_lock<std::mutex> &lk)
 {
-    const int q = (int)(taken_++ % slots_);
+    const int q = (int)(taken_++ % slots_->slots);
     const Part p = part_[q];
     pending_ -= p.bytes;
     lk.unlock();
-    const hipError_t e = hipEventSynchronize(ev_[q]);
+    const hipError_t e = hipEventSynchronize(slots_->ev[q]);
     if (e == hipSuccess)
-        memcpy(p.dst, pinned_ + (size_t)q * slot_, p.bytes);
+        memcpy(p.dst, slots_->mem + (size_t)q * slots_->slot, p.bytes);
     lk.lock();
     if (e != hipSuccess && err_ == hipSuccess)
         err_ = e;
@@ -127,7 +196,7 @@ void HostReader::work()
 void HostReader::spawn(std::unique_lock<std::mutex> &lk)
 {
     if (taken_ == 0) {
-        for (long long c = 0; c < issued_ && hipEventQuery(ev_[0]) == hipErrorNotReady; ++c)
+        for (long long c = 0; c < issued_ && hipEventQuery(slots_->ev[0]) == hipErrorNotReady; ++c)
             map_pages(part_[c].dst, part_[c].bytes);
         (void)hipGetLastError();  // "not ready" is none
         take(lk);
@@ -156,15 +225,21 @@ hipError_t HostReader::add(void *dst, const void *dev, size_t bytes)
     }
     hi_ = lo_ ? std::max(hi_, d + bytes) : d + bytes;
     lo_ = lo_ ? std::min(lo_, d) : d;
-    if (!pinned_ || known_to_runtime(dst)) {
+    const bool known = (slots_ || !tried_) && known_to_runtime(dst);
+    if (!known && !tried_) {
+        slots_ = lease(device_, n_, largest_);
+        tried_ = true;
+    }
+    if (known || !slots_) {
         hipError_t e = hipMemcpyAsync(dst, dev, bytes, hipMemcpyDeviceToHost, stream_);
         if (e == hipSuccess)  // (pageable copies left to queue up: 1.6 ms for 64^3, waited for one by one 0.5)
             e = hipStreamSynchronize(stream_);
         return err_ == hipSuccess ? err_ = e : err_;
     }
-    const size_t n = (bytes + slot_ - 1) / slot_, len = std::min(slot_, ((bytes + n - 1) / n + 4095) / 4096 * 4096);
+    const size_t slot = slots_->slot, n = (bytes + slot - 1) / slot;
+    const size_t len = std::min(slot, ((bytes + n - 1) / n + 4095) / 4096 * 4096);
     for (size_t a = 0; a < bytes; a += len) {
-        const int q = (int)(issued_ % slots_);
+        const int q = (int)(issued_ % slots_->slots);
         while (part_[q].busy) {
             spawn(lk);
             if (!part_[q].busy)
@@ -175,10 +250,9 @@ hipError_t HostReader::add(void *dst, const void *dev, size_t bytes)
                 cv_.wait(lk);
         }
         const size_t m = std::min(len, bytes - a);
-        hipError_t e = hipMemcpyAsync(pinned_ + (size_t)q * slot_, (const char *)dev + a, m, hipMemcpyDeviceToHost,
-                                      stream_);
+        hipError_t e = hipMemcpyAsync(slots_->mem + q * slot, (const char *)dev + a, m, hipMemcpyDeviceToHost, stream_);
         if (e == hipSuccess)
-            e = hipEventRecord(ev_[q], stream_);
+            e = hipEventRecord(slots_->ev[q], stream_);
         if (e != hipSuccess && err_ == hipSuccess)
             err_ = e;
         if (err_ != hipSuccess)
@@ -202,9 +276,16 @@ hipError_t HostReader::finish()
     cv_.wait(lk, [&] { return done_ == issued_; });
     lk.unlock();
     for (; nthreads_ > 0; --nthreads_) thread_[nthreads_ - 1].join();
-    if (err_ != hipSuccess)
-        (void)hipStreamSynchronize(stream_);  // nothing enqueued here outlives the call
-    return err_;
+    // Nothing enqueued here outlives the call; where that is not known the slots are not used again. (With the
+    // events alone waited for, the stream's next wait or its end takes 30 to 150 us more.)
+    const hipError_t e = slots_ || err_ != hipSuccess ? hipStreamSynchronize(stream_) : hipSuccess;
+    if (slots_ && e == hipSuccess) {
+        std::lock_guard<std::mutex> shared_lk(g_mu);
+        Shared &sh = g_shared[device_];
+        sh.idle[sh.nidle++] = slots_;
+    }
+    slots_ = nullptr;
+    return err_ != hipSuccess ? err_ : e;
 }
 
 }  // namespace fdtd

@@ -5,6 +5,9 @@
 // (the caller is one) copy them out, so that the pages are mapped by all of them; while the stream is still
 // busy with earlier work the caller maps pages ahead. All fields of 256^3 (404 MB): 40 ms before, 11 now; of
 // 128^3 6.1 and 1.7. Memory that the runtime knows (pinned, managed) still takes one copy of its own.
+//
+// The slots belong to the device and are leased for a read: made by each object, a first read of 96^3 FP32
+// fields took 2.9 ms (the runtime's copy 1.4), and its end 0.3 ms more.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -16,28 +19,35 @@
 
 namespace fdtd {
 
+// a copy and its event cost about 15 us beside the bytes: 256^3 FP32 fields (404 MB) arrive in 19 ms with
+// 512 KiB slots, 11 with 2 MiB; 31 ms by one thread, 12 by four, 11 by six
+constexpr size_t kSlot = 2 << 20;
+constexpr int kSlots = 8;
+constexpr int kSlotSets = 4;  // of a device
+
+struct PinnedSlots {
+    char *mem;
+    size_t slot;  // bytes of each
+    int slots;
+    hipEvent_t ev[kSlots];
+};
+
 // One read at a time: begin, add for each array in stream order (a source may be rewritten by work enqueued
 // after its add), finish. After an error finish is still called.
 class HostReader {
 public:
-    HostReader() = default;
+    HostReader();
     HostReader(const HostReader &) = delete;
     HostReader &operator=(const HostReader &) = delete;
-    ~HostReader() { release(); }
-    void release();
+    ~HostReader();
     // A read of n arrays of at most largest bytes each, in order on s; the device is current.
-    hipError_t begin(int device, hipStream_t s, int n, size_t largest);
+    void begin(int device, hipStream_t s, int n, size_t largest);
     hipError_t add(void *dst, const void *dev, size_t bytes);
     hipError_t finish();  // every array has arrived
 
 private:
-    // a copy and its event cost about 15 us beside the bytes: 256^3 FP32 fields (404 MB) arrive in 19 ms with
-    // 512 KiB slots, 11 with 2 MiB; 31 ms by one thread, 12 by four, 11 by six
-    static constexpr size_t kSlot = 2 << 20;
-    static constexpr int kSlots = 8, kThreads = 4;
+    static constexpr int kThreads = 4;
     static constexpr size_t kPerThread = 2 << 20;  // a thread costs about 20 us to start, 2 MiB 140 to copy
-
-    static constexpr size_t kWorth = 16 << 20;
 
     struct Part {
         char *dst;
@@ -48,14 +58,11 @@ private:
     void work();
     void spawn(std::unique_lock<std::mutex> &lk);
 
-    char *pinned_ = nullptr;
-    size_t slot_ = 0;
-    int slots_ = 0, events_ = 0;
-    size_t read_ = 0;  // bytes read so far
-    hipEvent_t ev_[kSlots] = {};
-
-    int device_ = 0;
+    int device_ = 0, n_ = 0;
+    size_t largest_ = 0;
     hipStream_t stream_ = nullptr;
+    PinnedSlots *slots_ = nullptr;  // leased from the first pageable array on; null: the runtime copies
+    bool tried_ = false;
     char *lo_ = nullptr, *hi_ = nullptr;  // hull of the destinations of this read
     size_t pending_ = 0;                  // bytes in slots that no thread has taken
     std::mutex mu_;

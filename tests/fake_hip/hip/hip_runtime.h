@@ -33,6 +33,7 @@ inline std::atomic<int> allocations{0}, live{0}, unrelaxed{0}, runtime_copies{0}
 inline std::atomic<bool> fail_alloc{false};
 inline std::set<const void *> known;                            // destinations that the runtime knows
 inline std::function<hipError_t()> on_sync = [] { return hipSuccess; };  // what waiting for an event does
+inline std::atomic<bool> stream_fails{false};                              // and for a stream
 
 struct Event {
     std::mutex m;
@@ -170,5 +171,5 @@ inline hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind
 inline hipError_t hipStreamSynchronize(hipStream_t s)
 {
     s->drain();
-    return hipSuccess;
+    return fake::stream_fails ? hipErrorUnknown : hipSuccess;
 }

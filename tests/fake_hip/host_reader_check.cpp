@@ -3,6 +3,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "host_read.h"
@@ -33,7 +34,7 @@ static void error_of_a_worker()
     };
     fake::Stream s;
     HostReader r;
-    CHECK(r.begin(0, &s, 2, 18 * MiB) == hipSuccess);
+    r.begin(0, &s, 2, 18 * MiB);
     CHECK(r.add(dst.data(), dev.data(), 18 * MiB) == hipSuccess);  // one part more than slots: workers hold three
     go.store(true, std::memory_order_relaxed);
     std::this_thread::sleep_for(std::chrono::milliseconds(200));
@@ -52,7 +53,7 @@ static void capture_mode()
     {
         HostReader r;
         for (size_t n : {MiB, 6 * MiB}) {
-            CHECK(r.begin(0, &s, 1, n) == hipSuccess);
+            r.begin(0, &s, 1, n);
             CHECK(r.add(dst.data(), dev.data(), n) == hipSuccess);
             CHECK(r.finish() == hipSuccess);
         }
@@ -63,16 +64,126 @@ static void capture_mode()
     CHECK(fake::mode == hipStreamCaptureModeGlobal);
 }
 
+// n arrays of bytes each into fresh memory, by one object; the values arrive.
+static hipError_t read(HostReader &r, int n, size_t bytes, bool runtime_knows = false)
+{
+    std::vector<std::vector<char>> dev(n), dst(n);
+    fake::Stream s;
+    r.begin(0, &s, n, bytes);
+    for (int q = 0; q < n; ++q) {
+        dev[q].assign(bytes, (char)(q + 1));
+        dst[q].resize(bytes);
+        if (runtime_knows)
+            fake::known.insert(dst[q].data());
+        if (r.add(dst[q].data(), dev[q].data(), bytes) != hipSuccess)
+            break;
+    }
+    const hipError_t e = r.finish();
+    if (runtime_knows)
+        fake::known.clear();
+    if (e == hipSuccess)
+        CHECK(dst == dev);
+    return e;
+}
+
+// Slots outlive the object that they were made for, and only slots that were leased are given back.
+static void slots_are_shared()
+{
+    for (int q = 0; q < 3; ++q) {
+        HostReader r;
+        CHECK(read(r, 6, 8 * MiB) == hipSuccess);
+        CHECK(fake::allocations == 1);
+    }
+    CHECK(fake::live == 1);
+}
+
+// Memory that the runtime knows takes no slots, and makes none.
+static void known_memory_makes_no_slots()
+{
+    HostReader r;
+    for (int q = 0; q < 3; ++q) CHECK(read(r, 6, 8 * MiB, true) == hipSuccess);
+    CHECK(fake::allocations == 0);
+}
+
+// Slots wait until the objects together have read enough, and the smallest reads do without.
+static void small_reads()
+{
+    for (int q = 0; q < 3; ++q) {
+        HostReader r;
+        CHECK(read(r, 6, MiB) == hipSuccess);
+    }
+    CHECK(fake::allocations == 0);
+    for (int q = 0; q < 20; ++q) {
+        HostReader r;
+        CHECK(read(r, 6, MiB / 2) == hipSuccess);
+    }
+    CHECK(fake::allocations == 0);
+    HostReader r;
+    CHECK(read(r, 6, MiB) == hipSuccess);
+    CHECK(fake::allocations == 1);
+}
+
+// Readers at the same time: a bounded number of slot sets, of which one stays when the last object goes.
+static void readers_at_once()
+{
+    {
+        HostReader r[8];
+        std::vector<std::thread> t;
+        for (auto &x : r)
+            t.emplace_back([&x] {
+                for (int q = 0; q < 6; ++q) CHECK(read(x, 3, 5 * MiB) == hipSuccess);
+            });
+        for (auto &x : t) x.join();
+        CHECK(fake::live >= 1 && fake::live <= 4);
+    }
+    CHECK(fake::live == 1);
+}
+
+// No pinned memory to be had: the runtime copies.
+static void no_pinned_memory()
+{
+    fake::fail_alloc = true;
+    HostReader r;
+    for (int q = 0; q < 3; ++q) CHECK(read(r, 6, 8 * MiB) == hipSuccess);
+    fake::fail_alloc = false;
+    CHECK(read(r, 6, 8 * MiB) == hipSuccess);
+    CHECK(fake::allocations == 1);
+}
+
+// After a stream that cannot be waited for, its copies may still be to come: their slots are not used again.
+static void slots_of_a_failed_stream()
+{
+    HostReader r;
+    CHECK(read(r, 6, 8 * MiB) == hipSuccess);
+    fake::on_sync = [] { return hipErrorUnknown; };
+    fake::stream_fails = true;
+    CHECK(read(r, 6, 8 * MiB) == hipErrorUnknown);
+    fake::on_sync = [] { return hipSuccess; };
+    fake::stream_fails = false;
+    CHECK(fake::allocations == 1 && fake::live == 1);
+    for (int q = 0; q < 3; ++q) CHECK(read(r, 6, 8 * MiB) == hipSuccess);
+    CHECK(fake::allocations == 2);
+}
+
 int main(int argc, char **argv)
 {
     for (int a = 1; a < argc; ++a) {
         const std::string what = argv[a];
-        if (what == "error_of_a_worker")
-            error_of_a_worker();
-        else if (what == "capture_mode")
-            capture_mode();
-        else
-            CHECK(!"known check");
+        bool known = false;
+        for (const auto &c : std::initializer_list<std::pair<const char *, void (*)()>>{
+                 {"error_of_a_worker", error_of_a_worker},
+                 {"capture_mode", capture_mode},
+                 {"slots_are_shared", slots_are_shared},
+                 {"known_memory_makes_no_slots", known_memory_makes_no_slots},
+                 {"small_reads", small_reads},
+                 {"readers_at_once", readers_at_once},
+                 {"no_pinned_memory", no_pinned_memory},
+                 {"slots_of_a_failed_stream", slots_of_a_failed_stream}})
+            if (what == c.first) {
+                known = true;
+                c.second();
+            }
+        CHECK(known);
     }
     printf("ok\n");
 }
