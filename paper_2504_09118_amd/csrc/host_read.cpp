@@ -225,7 +225,7 @@ hipError_t HostReader::add(void *dst, const void *dev, size_t bytes)
     }
     hi_ = lo_ ? std::max(hi_, d + bytes) : d + bytes;
     lo_ = lo_ ? std::min(lo_, d) : d;
-    const bool known = (slots_ || !tried_) && known_to_runtime(dst);
+    const bool known = (slots_ || !tried_) && ((uintptr_t)dev % 16 != 0 || known_to_runtime(dst));
     if (!known && !tried_) {
         slots_ = lease(device_, n_, largest_);
         tried_ = true;
@@ -250,7 +250,7 @@ hipError_t HostReader::add(void *dst, const void *dev, size_t bytes)
                 cv_.wait(lk);
         }
         const size_t m = std::min(len, bytes - a);
-        hipError_t e = hipMemcpyAsync(slots_->mem + q * slot, (const char *)dev + a, m, hipMemcpyDeviceToHost, stream_);
+        hipError_t e = launch_host_copy(slots_->mem + q * slot, (const char *)dev + a, m, stream_);
         if (e == hipSuccess)
             e = hipEventRecord(slots_->ev[q], stream_);
         if (e != hipSuccess && err_ == hipSuccess)

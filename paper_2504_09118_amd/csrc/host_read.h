@@ -1,10 +1,11 @@
 // Device arrays into pageable host memory.
 //
 // The runtime's own copy into fresh pageable memory pins the caller's pages chunk by chunk: 4.4 GB/s from 1
-// MiB on, where the link carries 57. Here the copy engine fills pinned slots and up to kThreads threads
-// (the caller is one) copy them out, so that the pages are mapped by all of them; while the stream is still
-// busy with earlier work the caller maps pages ahead. All fields of 256^3 (404 MB): 40 ms before, 11 now; of
-// 128^3 6.1 and 1.7. Memory that the runtime knows (pinned, managed) still takes one copy of its own.
+// MiB on, 17 into mapped pages, where the link carries 57. Here a kernel fills pinned slots and up to kThreads
+// threads (the caller is one) copy them out, so that the pages are mapped by all of them; while the stream is
+// still busy with earlier work the caller maps pages ahead. Fresh pages and mapped ones, the runtime's copy
+// in brackets: all FP32 fields of 256^3 (404 MB) 12.3 and 8.5 ms (40 and 23), of 128^3 2.6 and 1.2 (6.1 and
+// 3.0). Memory that the runtime knows (pinned, managed) still takes one copy of its own.
 //
 // The slots belong to the device and are leased for a read: made by each object, a first read of 96^3 FP32
 // fields took 2.9 ms (the runtime's copy 1.4), and its end 0.3 ms more.
@@ -19,8 +20,8 @@
 
 namespace fdtd {
 
-// a copy and its event cost about 15 us beside the bytes: 256^3 FP32 fields (404 MB) arrive in 19 ms with
-// 512 KiB slots, 11 with 2 MiB; 31 ms by one thread, 12 by four, 11 by six
+// slots of 2 MiB and four threads: 256^3 FP32 fields arrived in 19 ms with 512 KiB slots, 11 with 2 MiB; in 31
+// by one thread, 12 by four, 11 by six (slots filled by the runtime's copies)
 constexpr size_t kSlot = 2 << 20;
 constexpr int kSlots = 8;
 constexpr int kSlotSets = 4;  // of a device
@@ -31,6 +32,9 @@ struct PinnedSlots {
     int slots;
     hipEvent_t ev[kSlots];
 };
+
+// A kernel that copies device memory to pinned memory, both on 16-byte boundaries (k_host_copy.hip).
+hipError_t launch_host_copy(void *dst, const void *src, size_t bytes, hipStream_t s);
 
 // One read at a time: begin, add for each array in stream order (a source may be rewritten by work enqueued
 // after its add), finish. After an error finish is still called.

@@ -1,5 +1,6 @@
 // Checks of the host reader against the HIP calls of hip/hip_runtime.h here, one per argument; prints "ok".
 #include <chrono>
+#include <cstdint>
 #include <cstdio>
 #include <cstdlib>
 #include <string>
@@ -15,6 +16,16 @@
             exit(1);                                                                                                 \
         }                                                                                                            \
     } while (0)
+
+namespace fdtd {
+hipError_t launch_host_copy(void *dst, const void *src, size_t bytes, hipStream_t s)
+{
+    if ((uintptr_t)dst % 16 != 0 || (uintptr_t)src % 16 != 0)
+        return hipErrorInvalidValue;
+    s->push([=] { memcpy(dst, src, bytes); });
+    return hipSuccess;
+}
+}  // namespace fdtd
 
 using fdtd::HostReader;
 static const size_t MiB = 1 << 20;
@@ -123,6 +134,20 @@ static void small_reads()
     CHECK(fake::allocations == 1);
 }
 
+// Slots are filled by the kernel, whatever the sizes; a source off its 16-byte boundary is the runtime's.
+static void filled_by_the_kernel()
+{
+    HostReader r;
+    for (size_t odd : {0, 4, 4095}) CHECK(read(r, 6, 8 * MiB + odd) == hipSuccess);
+    CHECK(fake::allocations == 1 && fake::runtime_copies == 0);
+    std::vector<char> dev(6 * MiB + 4, 7), dst(6 * MiB);
+    fake::Stream s;
+    r.begin(0, &s, 1, 6 * MiB);
+    CHECK(r.add(dst.data(), dev.data() + 4, 6 * MiB) == hipSuccess);
+    CHECK(r.finish() == hipSuccess);
+    CHECK(fake::runtime_copies == 1 && memcmp(dst.data(), dev.data() + 4, 6 * MiB) == 0);
+}
+
 // Readers at the same time: a bounded number of slot sets, of which one stays when the last object goes.
 static void readers_at_once()
 {
@@ -176,6 +201,7 @@ int main(int argc, char **argv)
                  {"slots_are_shared", slots_are_shared},
                  {"known_memory_makes_no_slots", known_memory_makes_no_slots},
                  {"small_reads", small_reads},
+                 {"filled_by_the_kernel", filled_by_the_kernel},
                  {"readers_at_once", readers_at_once},
                  {"no_pinned_memory", no_pinned_memory},
                  {"slots_of_a_failed_stream", slots_of_a_failed_stream}})

@@ -34,7 +34,8 @@ def check(tmp_path_factory):
     return run
 
 
-@pytest.mark.parametrize("name", ["error_of_a_worker", "capture_mode", "slots_are_shared", "known_memory_makes_no_slots",
-                                  "small_reads", "readers_at_once", "no_pinned_memory", "slots_of_a_failed_stream"])
+@pytest.mark.parametrize("name", [
+    "error_of_a_worker", "capture_mode", "slots_are_shared", "known_memory_makes_no_slots", "small_reads",
+    "filled_by_the_kernel", "readers_at_once", "no_pinned_memory", "slots_of_a_failed_stream"])
 def test_reader(check, name):
     check(name)
