@@ -4,7 +4,7 @@
 // MiB on, 17 into mapped pages, where the link carries 57. Here a kernel fills pinned slots and up to kThreads
 // threads (the caller is one) copy them out, so that the pages are mapped by all of them; while the stream is
 // still busy with earlier work the caller maps pages ahead. Fresh pages and mapped ones, the runtime's copy
-// in brackets: all FP32 fields of 256^3 (404 MB) 12.3 and 8.5 ms (40 and 23), of 128^3 2.6 and 1.2 (6.1 and
+// in brackets: all FP32 fields of 256^3 (404 MB) 11.3 and 8.5 ms (40 and 23), of 128^3 2.1 and 1.2 (6.1 and
 // 3.0). Memory that the runtime knows (pinned, managed) still takes one copy of its own.
 //
 // The slots belong to the device and are leased for a read: made by each object, a first read of 96^3 FP32
