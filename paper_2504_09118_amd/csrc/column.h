@@ -43,9 +43,9 @@ constexpr int kNR = kColumnRows;  // rows per lane
 constexpr int kCols = 64;
 
 // Waves of a workgroup: 16 of 128 registers where the rings fit (FP32 with one coefficient array: 51
-// values a row at 4 stages), else 12 of 168. A spilled register inside the plane loop costs more than
-// the smaller window, because its reload waits for every load issued before it (Ce and Ch, 3 stages:
-// 72 us with 16 waves and 20 spills, 43 us with 12).
+// values a row at 4 stages), else 12 of 168, or 8 of 256. A spilled register inside the plane loop costs
+// more than the smaller window, because its reload waits for every load issued before it (Ce and Ch, 3
+// stages: 72 us with 16 waves and 20 spills, 43 us with 12).
 template <typename S, int TS, bool CE_ARR, bool CH_ARR>
 constexpr int column_waves()
 {

@@ -132,8 +132,14 @@ int temporal_width(int variant);
 // what a variant-0 temporal step runs for a state that the last-level cache holds (nt_stores false).
 // Rows per lane, waves of a workgroup, x-y windows of a grid.
 constexpr int kColumnRows = 2;
+// Waves of a full workgroup: as many as hold the shape in registers. 16-bit storage with both coefficient
+// arrays: 12 at two steps (16 waves spill 14 to 47 values a lane inside the plane loop: 160x96x128, FP16 with
+// residuals, 36.7 us a step, 12 waves 17.9; FP16 19.2 and 13.9), 8 at four (12 waves spill 22 to 72: 38.6 and
+// 16.0; FP16 15.6 and 12.1).
 constexpr int column_waves_of(bool half, int ts, bool ce_arr, bool ch_arr)
 {
+    if (half && ce_arr && ch_arr)
+        return ts == 1 ? 16 : ts < 4 ? 12 : 8;
     return ts > 2 && ((ce_arr && ch_arr) || (half && (ce_arr || ch_arr))) ? 12 : 16;
 }
 inline void column_windows(int nx, int ny, int ts, int waves, int *ntx, int *nty)
