@@ -277,9 +277,11 @@ int env_int(const char *name, int dflt)
     return atoi(v);
 }
 
-// z-split of a temporal sweep of ts steps: the default one of its own tile shape (a remainder sweep's
-// windows differ from a full one's), or the one that the schedule names.
-int zsplit_of(fdtd_t h, int ts) { return h->tz_default ? h->tz_own[ts] : h->tzchunk; }
+// z-split of a temporal sweep of ts steps: the one that the schedule names for a full sweep, the default one
+// of its own tile shape for a remainder, whose windows differ (5 steps in the schedule that the search chose,
+// with the full sweep's split and with its own: 160x96x128 FP16 62.9 and 57.5 us, 128^3 70.6 and 65.5, 160^3
+// FP32 171 and 162; 64^3 FP16 23.8 and 25.9).
+int zsplit_of(fdtd_t h, int ts) { return ts == h->tb || h->tz_fixed ? h->tzchunk : h->tz_own[ts]; }
 
 template <typename T>
 hipError_t launch_one(fdtd_t h, int kernel, int ts, unsigned *queue)
@@ -507,19 +509,42 @@ int column_zsplit(const Geom &g, int ts, int wide, bool pairs, int device)
     const int cus = device_cus(device);
     double best = -1.0;
     int zc_best = 1;
-    for (int zc = 1; zc <= g.nz; ++zc) {
-        if ((g.nz + zc - 1) / zc > kTemporalMaxChunk && zc < g.nz)
-            continue;
-        const double cost =
-            std::min(column_cost(g, ts, wide, pairs, zc, cus), column_cost(g, ts, kNarrowWaves, pairs, zc, cus));
-        if (best < 0 || cost < best) {
-            best = cost;
-            zc_best = zc;
+    for (int kc = g.nz;;) {  // planes of a chunk: each value that a split gives, with the fewest chunks
+        const int zc = (g.nz + kc - 1) / kc;
+        if (kc <= kTemporalMaxChunk || kc == 1) {
+            const double cost =
+                std::min(column_cost(g, ts, wide, pairs, zc, cus), column_cost(g, ts, kNarrowWaves, pairs, zc, cus));
+            if (best < 0 || cost < best) {
+                best = cost;
+                zc_best = zc;
+            }
         }
+        if (kc == 1)
+            return zc_best;
+        const int next = (g.nz + kc - 2) / (kc - 1);  // the fewest chunks of less than kc planes
+        kc = (g.nz + next - 1) / next;
     }
-    return zc_best;
 }
 }  // namespace fdtd
+
+namespace {
+
+// Default z-split of a temporal sweep of ts steps (fdtd_create states the rule).
+int own_split(const fdtd_solver *h, int ts, int variant)
+{
+    const Geom &g = h->plan.g;
+    if (variant == 0 && !h->nt_stores) {
+        const bool half = is16(h->storage), ce = h->ce_arr, ch = h->ch_arr;
+        return fdtd::column_zsplit(g, ts, fdtd::column_waves_of(half, ts, ce, ch),
+                                   fdtd::column_narrow_pairs(half, ts, ce, ch), h->device);
+    }
+    const int tv = ts > 3 ? 0 : variant;
+    const int own = fdtd::temporal_own_rows(ts, tv), w = fdtd::temporal_width(tv);
+    const long long tiles = (long long)((g.nx + w - 1) / w) * ((g.ny + own - 1) / own);
+    return best_zsplit(tiles, g.nz, 2 * ts - 1, 8, device_cus(h->device), kTemporalMaxChunk);
+}
+
+}  // namespace
 
 extern "C" {
 
@@ -697,21 +722,10 @@ int fdtd_create(int nx, int ny, int nz, double dx, double dt, const fdtd_coef *c
     // (the tiles of one XCD drift apart over a long chunk and share fewer halo lines in L2: 1024^3 ran
     // 3 % faster in 342-plane chunks than in one 1024-plane chunk). The column form, where small
     // cavities leave CUs idle: down to one plane (32^3, 4 steps: 32 chunks 14 us, 8 chunks 18 us).
-    for (int ts = 1; ts <= 4; ++ts) {
-        if (h->tvariant == 0 && !h->nt_stores) {
-            const bool half = is16(h->storage), ce = h->ce_arr, ch = h->ch_arr;
-            h->tz_own[ts] = fdtd::column_zsplit(p.g, ts, fdtd::column_waves_of(half, ts, ce, ch),
-                                                fdtd::column_narrow_pairs(half, ts, ce, ch), o->device);
-        } else {
-            const int tv = ts > 3 ? 0 : h->tvariant;
-            const int own = fdtd::temporal_own_rows(ts, tv), w = fdtd::temporal_width(tv);
-            const long long tiles = (long long)((nx + w - 1) / w) * ((ny + own - 1) / own);
-            h->tz_own[ts] = best_zsplit(tiles, nz, 2 * ts - 1, 8, device_cus(o->device), kTemporalMaxChunk);
-        }
-    }
+    for (int ts = 1; ts <= 4; ++ts) h->tz_own[ts] = own_split(h, ts, h->tvariant);
     h->tzchunk = env_int("FDTD_TZCHUNKS", 0);
-    h->tz_default = h->tzchunk <= 0;
-    if (h->tz_default)
+    h->tz_fixed = h->tzchunk > 0;
+    if (!h->tz_fixed)
         h->tzchunk = h->tz_own[h->tb];
     if (o->stream) {
         h->stream = (hipStream_t)o->stream;
@@ -1055,9 +1069,10 @@ void apply_schedule(fdtd_t h, const fdtd_schedule *sc)
     h->kernel = sc->kernel;
     if (sc->kernel == FDTD_KERNEL_TEMPORAL) {
         h->tb = sc->tb_steps;
-        h->tvariant = sc->variant;
         h->tzchunk = sc->zchunks;
-        h->tz_default = false;
+        if (h->tvariant != sc->variant)
+            for (int ts = 1; ts <= 4; ++ts) h->tz_own[ts] = own_split(h, ts, sc->variant);
+        h->tvariant = sc->variant;
     } else {
         h->tb = 1;
         if (sc->kernel == FDTD_KERNEL_SLAB)
@@ -1091,18 +1106,20 @@ std::vector<fdtd_schedule> schedule_candidates(fdtd_t h)
             for (int zc : zcs) add(FDTD_KERNEL_SLAB, 1, v, zc);
         }
     }
-    // the temporal default split need not be a power of two: try it too
-    std::vector<int> tzcs = zcs;
-    if (std::find(tzcs.begin(), tzcs.end(), h->tzchunk) == tzcs.end())
-        tzcs.push_back(h->tzchunk);
     // 16-bit storage rounds the state at the end of every sweep, so the steps per sweep set
     // the numerics: the search keeps the solver's own tb there and varies only the tiling
     const int tb_lo = is16(h->storage) ? h->tb : 1, tb_hi = is16(h->storage) ? h->tb : 4;
     if (h->storage != FDTD_F64)
         for (int tb = tb_lo; tb <= tb_hi; ++tb)
             for (int v = 0; v < 2; ++v)
-                if (v == 0 || tb <= 3)
+                if (v == 0 || tb <= 3) {
+                    // the solver's own split and the default one need not be powers of two: try them too
+                    std::vector<int> tzcs = zcs;
+                    for (int zc : {h->tzchunk, own_split(h, tb, v)})
+                        if (std::find(tzcs.begin(), tzcs.end(), zc) == tzcs.end())
+                            tzcs.push_back(zc);
                     for (int zc : tzcs) add(FDTD_KERNEL_TEMPORAL, tb, v, zc);
+                }
     return out;
 }
 

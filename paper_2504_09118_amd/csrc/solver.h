@@ -20,7 +20,7 @@ struct fdtd_solver {
     bool aniso;       // d[1] or d[2] differs from dx
     int storage, kernel, tb, device, zchunk, tzchunk, variant, tvariant;
     int tz_own[5];    // default z-split of a temporal sweep of 1..4 steps
-    bool tz_default;  // no schedule was chosen: each sweep takes its own default split
+    bool tz_fixed;    // FDTD_TZCHUNKS names the split of every sweep
     hipStream_t stream;
     bool own_stream;
     char *arena;
