@@ -283,6 +283,13 @@ int env_int(const char *name, int dflt)
 // FP32 171 and 162; 64^3 FP16 23.8 and 25.9).
 int zsplit_of(fdtd_t h, int ts) { return ts == h->tb || h->tz_fixed ? h->tzchunk : h->tz_own[ts]; }
 
+// Whether a single step of the temporal schedule runs in slabs (single_slabs; a chosen split is the column
+// form's).
+bool takes_slabs(fdtd_t h)
+{
+    return h->slab1 > 0 && h->tvariant == 0 && (h->tb != 1 || h->tzchunk == h->tz_own[1]);
+}
+
 template <typename T>
 hipError_t launch_one(fdtd_t h, int kernel, int ts, unsigned *queue)
 {
@@ -299,6 +306,9 @@ hipError_t launch_one(fdtd_t h, int kernel, int ts, unsigned *queue)
         if (kernel == FDTD_KERNEL_SLAB)
             e = fdtd::launch_slab_step<T>(h->plan.g, fields_of<T>(h, h->cur), fields_of<T>(h, 1 - h->cur), c,
                                           h->zchunk, h->variant, h->stream, h->nt_stores);
+        else if (kernel == FDTD_KERNEL_TEMPORAL && ts == 1 && takes_slabs(h))
+            e = fdtd::launch_slab_step<T>(h->plan.g, fields_of<T>(h, h->cur), fields_of<T>(h, 1 - h->cur), c, h->slab1,
+                                          0, h->stream, false);
         else if (kernel == FDTD_KERNEL_TEMPORAL)
             e = fdtd::launch_temporal_step<T>(h->plan.g, fields_of<T>(h, h->cur), fields_of<T>(h, 1 - h->cur), c,
                                               zsplit_of(h, ts), ts, h->tvariant, h->stream, h->nt_stores, queue);
@@ -483,7 +493,8 @@ int device_cus(int device)
 // when max_planes > 0, of at most max_planes (where nz allows).
 constexpr int kTemporalMaxChunk = 384;
 
-int best_zsplit(long long tiles, int nz, int redo, int min_planes, int cus, int max_planes = 0)
+int best_zsplit(long long tiles, int nz, int redo, int min_planes, int cus, int max_planes = 0,
+                long long *least = nullptr)
 {
     long long best = -1;
     int zc_best = 1;
@@ -498,13 +509,15 @@ int best_zsplit(long long tiles, int nz, int redo, int min_planes, int cus, int 
             zc_best = zc;
         }
     }
+    if (least)
+        *least = best;
     return zc_best;
 }
 
 }  // namespace
 
 namespace fdtd {
-int column_zsplit(const Geom &g, int ts, int wide, bool pairs, int device)
+int column_zsplit(const Geom &g, int ts, int wide, bool pairs, int device, double *least)
 {
     const int cus = device_cus(device);
     double best = -1.0;
@@ -519,8 +532,11 @@ int column_zsplit(const Geom &g, int ts, int wide, bool pairs, int device)
                 zc_best = zc;
             }
         }
-        if (kc == 1)
+        if (kc == 1) {
+            if (least)
+                *least = best;
             return zc_best;
+        }
         const int next = (g.nz + kc - 2) / (kc - 1);  // the fewest chunks of less than kc planes
         kc = (g.nz + next - 1) / next;
     }
@@ -529,19 +545,49 @@ int column_zsplit(const Geom &g, int ts, int wide, bool pairs, int device)
 
 namespace {
 
-// Default z-split of a temporal sweep of ts steps (fdtd_create states the rule).
-int own_split(const fdtd_solver *h, int ts, int variant)
+// Default z-split of a temporal sweep of ts steps in its form (fdtd_create states the rule).
+int own_split(const fdtd_solver *h, int ts, int variant, bool column, double *least = nullptr)
 {
     const Geom &g = h->plan.g;
-    if (variant == 0 && !h->nt_stores) {
+    if (column) {
         const bool half = is16(h->storage), ce = h->ce_arr, ch = h->ch_arr;
         return fdtd::column_zsplit(g, ts, fdtd::column_waves_of(half, ts, ce, ch),
-                                   fdtd::column_narrow_pairs(half, ts, ce, ch), h->device);
+                                   fdtd::column_narrow_pairs(half, ts, ce, ch), h->device, least);
     }
     const int tv = ts > 3 ? 0 : variant;
     const int own = fdtd::temporal_own_rows(ts, tv), w = fdtd::temporal_width(tv);
     const long long tiles = (long long)((g.nx + w - 1) / w) * ((g.ny + own - 1) / own);
-    return best_zsplit(tiles, g.nz, 2 * ts - 1, 8, device_cus(h->device), kTemporalMaxChunk);
+    long long cost = 0;
+    const int zc = best_zsplit(tiles, g.nz, 2 * ts - 1, 8, device_cus(h->device), kTemporalMaxChunk, &cost);
+    if (least)
+        *least = (double)cost;
+    return zc;
+}
+
+void own_splits(fdtd_t h)
+{
+    for (int ts = 1; ts <= 4; ++ts) h->tz_own[ts] = own_split(h, ts, h->tvariant, h->tvariant == 0 && !h->nt_stores);
+}
+
+// The form of single steps of a temporal schedule of FP32 fields that the last-level cache holds: the slab
+// kernel's z-split, or 0 for the column form. A column sweep of one step gains nothing from its rings and
+// pays for its windows, slabs of 128 columns with one halo row do less where the cavity fills the chip. By
+// the costs of the two (planes of a workgroup, waves of workgroups), slabs from 0.8 of the slab's on: 128^3
+// with both arrays (1.16) 36.5 us in column form, 28.8 in slabs, 35.3 in the form for large states; 128x64x276
+// 41.9 and 30.7 (39.0); 192x100x199 vacuum (0.84) 39.4 and 35.0 (37.6); below, 96^3 vacuum (0.72) 12.2 and 12.9,
+// 64^3 7.3 and 11.9.
+int single_slabs(const fdtd_solver *h)
+{
+    if (h->storage != FDTD_F32 || h->nt_stores || h->form_fixed || h->tz_fixed)
+        return 0;
+    const Geom &g = h->plan.g;
+    const int own = fdtd::slab_rows(0) - 2, w = fdtd::slab_width(0);
+    const long long tiles = (long long)((g.nx + w - 1) / w) * ((g.ny + own - 1) / own);
+    long long slab = 0;
+    double column = 0;
+    const int zc = best_zsplit(tiles, g.nz, 1, 4, device_cus(h->device), 0, &slab);
+    (void)own_split(h, 1, 0, true, &column);
+    return column >= 0.8 * (double)slab ? zc : 0;
 }
 
 }  // namespace
@@ -680,7 +726,8 @@ int fdtd_create(int nx, int ny, int nz, double dx, double dt, const fdtd_coef *c
         const size_t streamed = 12 * p.fbox_bytes + ((h->ce_arr ? 3 : 0) + (h->ch_arr ? 3 : 0)) * p.cbox_bytes;
         h->nt_stores = streamed > fdtd::kStreamCacheBytes;
         const int force = env_int("FDTD_NT_STORES", -1);  // 0 / 1 overrides the size rule
-        if (force == 0 || force == 1)
+        h->form_fixed = force == 0 || force == 1;
+        if (h->form_fixed)
             h->nt_stores = force == 1;
     }
     const int slab_v = h->storage == FDTD_F64 ? 3 : h->variant;
@@ -722,9 +769,10 @@ int fdtd_create(int nx, int ny, int nz, double dx, double dt, const fdtd_coef *c
     // (the tiles of one XCD drift apart over a long chunk and share fewer halo lines in L2: 1024^3 ran
     // 3 % faster in 342-plane chunks than in one 1024-plane chunk). The column form, where small
     // cavities leave CUs idle: down to one plane (32^3, 4 steps: 32 chunks 14 us, 8 chunks 18 us).
-    for (int ts = 1; ts <= 4; ++ts) h->tz_own[ts] = own_split(h, ts, h->tvariant);
+    own_splits(h);
     h->tzchunk = env_int("FDTD_TZCHUNKS", 0);
     h->tz_fixed = h->tzchunk > 0;
+    h->slab1 = single_slabs(h);
     if (!h->tz_fixed)
         h->tzchunk = h->tz_own[h->tb];
     if (o->stream) {
@@ -1070,9 +1118,8 @@ void apply_schedule(fdtd_t h, const fdtd_schedule *sc)
     if (sc->kernel == FDTD_KERNEL_TEMPORAL) {
         h->tb = sc->tb_steps;
         h->tzchunk = sc->zchunks;
-        if (h->tvariant != sc->variant)
-            for (int ts = 1; ts <= 4; ++ts) h->tz_own[ts] = own_split(h, ts, sc->variant);
         h->tvariant = sc->variant;
+        own_splits(h);
     } else {
         h->tb = 1;
         if (sc->kernel == FDTD_KERNEL_SLAB)
@@ -1115,7 +1162,7 @@ std::vector<fdtd_schedule> schedule_candidates(fdtd_t h)
                 if (v == 0 || tb <= 3) {
                     // the solver's own split and the default one need not be powers of two: try them too
                     std::vector<int> tzcs = zcs;
-                    for (int zc : {h->tzchunk, own_split(h, tb, v)})
+                    for (int zc : {h->tzchunk, own_split(h, tb, v, v == 0 && !h->nt_stores)})
                         if (std::find(tzcs.begin(), tzcs.end(), zc) == tzcs.end())
                             tzcs.push_back(zc);
                     for (int zc : tzcs) add(FDTD_KERNEL_TEMPORAL, tb, v, zc);

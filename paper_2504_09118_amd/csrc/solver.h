@@ -21,6 +21,8 @@ struct fdtd_solver {
     int storage, kernel, tb, device, zchunk, tzchunk, variant, tvariant;
     int tz_own[5];    // default z-split of a temporal sweep of 1..4 steps
     bool tz_fixed;    // FDTD_TZCHUNKS names the split of every sweep
+    bool form_fixed;  // FDTD_NT_STORES names the form of every sweep
+    int slab1;        // z-split of single steps in slabs, or 0
     hipStream_t stream;
     bool own_stream;
     char *arena;
@@ -50,7 +52,8 @@ int solver_check(fdtd_t h);
 int solver_device_fail(fdtd_t h, hipError_t e, const char *what);
 
 // z-split of a column sweep of ts steps with wide waves a workgroup or kNarrowWaves, with pairs two of those a CU.
-int column_zsplit(const Geom &g, int ts, int wide, bool pairs, int device);
+// least: its cost.
+int column_zsplit(const Geom &g, int ts, int wide, bool pairs, int device, double *least = nullptr);
 
 // fdtd_step with the temporal sweeps' scheduling counters (kSchedWords words, zero
 // before and after each launch) taken from queue instead of the solver's arena.
