@@ -290,6 +290,9 @@ bool takes_slabs(fdtd_t h)
     return h->slab1 > 0 && h->tvariant == 0 && (h->tb != 1 || h->tzchunk == h->tz_own[1]);
 }
 
+// Stores of a temporal sweep: variant 0 with default-policy ones is the column form.
+bool streams(fdtd_t h, int ts) { return h->tvariant == 0 ? !h->column[ts] : h->nt_stores; }
+
 template <typename T>
 hipError_t launch_one(fdtd_t h, int kernel, int ts, unsigned *queue)
 {
@@ -299,7 +302,7 @@ hipError_t launch_one(fdtd_t h, int kernel, int ts, unsigned *queue)
         // 16-bit storage is built for the temporal sweep only (ts = 1 for single steps)
         (void)kernel;
         e = fdtd::launch_temporal_step<T>(h->plan.g, fields_of<T>(h, h->cur), fields_of<T>(h, 1 - h->cur), c,
-                                          zsplit_of(h, ts), ts, h->tvariant, h->stream, h->nt_stores, queue);
+                                          zsplit_of(h, ts), ts, h->tvariant, h->stream, streams(h, ts), queue);
     } else {
         if (kernel == FDTD_KERNEL_PLAIN)
             return fdtd::launch_plain_step<T>(h->plan.g, fields_of<T>(h, h->cur), c, h->stream);
@@ -311,7 +314,7 @@ hipError_t launch_one(fdtd_t h, int kernel, int ts, unsigned *queue)
                                           0, h->stream, false);
         else if (kernel == FDTD_KERNEL_TEMPORAL)
             e = fdtd::launch_temporal_step<T>(h->plan.g, fields_of<T>(h, h->cur), fields_of<T>(h, 1 - h->cur), c,
-                                              zsplit_of(h, ts), ts, h->tvariant, h->stream, h->nt_stores, queue);
+                                              zsplit_of(h, ts), ts, h->tvariant, h->stream, streams(h, ts), queue);
         else
             e = fdtd::launch_fused_step<T>(h->plan.g, fields_of<T>(h, h->cur), fields_of<T>(h, 1 - h->cur), c,
                                            h->zchunk, h->stream);
@@ -564,9 +567,36 @@ int own_split(const fdtd_solver *h, int ts, int variant, bool column, double *le
     return zc;
 }
 
+// Whether a temporal sweep of ts steps takes the column form: variant 0 of a state that the last-level cache
+// holds, save sweeps of plain 16-bit fields that the form for large states runs faster. Its windows hold more
+// cells of their own (64 columns of 64 to the column form's 58 of 64, 22 rows to 18 with a coefficient array),
+// which counts once the cavity fills the chip. By the costs of the two, c and s: three steps without arrays from
+// c = 0.95 s + 3 on (128x64x600 BF16 71.8 us a sweep in columns, 59.5 streaming; 126x122x296 61.9 and 58.1; below,
+// 192x192x93 49.1 and 48.5, 126x122x164 40 and 45), with one array from 1.5 s on (128x64x554 75.8 and 64.2, 192x100x186
+// 59.2 and 55.9; below, 128x128x194 51.7 and 52.7, 192x100x119 0.9 of streaming), two steps with both from 1.72 s
+// on (128x128x208 52.4 and 48.3; 256x256x61 0.97 of streaming). Four steps and single ones gain by the column form
+// at every size.
+bool column_form(const fdtd_solver *h, int ts, int variant)
+{
+    if (variant != 0 || h->nt_stores)
+        return false;
+    if (h->form_fixed || !is16(h->storage) || is_comp(h->storage) || ts == 1 || ts == 4)
+        return true;
+    const int arrays = h->ce_arr + h->ch_arr;
+    if (ts == 2 ? arrays != 2 : arrays == 2)
+        return true;
+    double c = 0, s = 0;
+    (void)own_split(h, ts, 0, true, &c);
+    (void)own_split(h, ts, 0, false, &s);
+    return !(arrays == 0 ? c >= 0.95 * s + 3 : c >= (arrays == 1 ? 1.5 : 1.72) * s);
+}
+
 void own_splits(fdtd_t h)
 {
-    for (int ts = 1; ts <= 4; ++ts) h->tz_own[ts] = own_split(h, ts, h->tvariant, h->tvariant == 0 && !h->nt_stores);
+    for (int ts = 1; ts <= 4; ++ts) {
+        h->column[ts] = column_form(h, ts, h->tvariant);
+        h->tz_own[ts] = own_split(h, ts, h->tvariant, h->column[ts]);
+    }
 }
 
 // The form of single steps of a temporal schedule of FP32 fields that the last-level cache holds: the slab
@@ -1162,7 +1192,7 @@ std::vector<fdtd_schedule> schedule_candidates(fdtd_t h)
                 if (v == 0 || tb <= 3) {
                     // the solver's own split and the default one need not be powers of two: try them too
                     std::vector<int> tzcs = zcs;
-                    for (int zc : {h->tzchunk, own_split(h, tb, v, v == 0 && !h->nt_stores)})
+                    for (int zc : {h->tzchunk, own_split(h, tb, v, column_form(h, tb, v))})
                         if (std::find(tzcs.begin(), tzcs.end(), zc) == tzcs.end())
                             tzcs.push_back(zc);
                     for (int zc : tzcs) add(FDTD_KERNEL_TEMPORAL, tb, v, zc);

@@ -23,6 +23,7 @@ struct fdtd_solver {
     bool tz_fixed;    // FDTD_TZCHUNKS names the split of every sweep
     bool form_fixed;  // FDTD_NT_STORES names the form of every sweep
     int slab1;        // z-split of single steps in slabs, or 0
+    bool column[5];   // whether a temporal sweep of 1..4 steps takes the column form
     hipStream_t stream;
     bool own_stream;
     char *arena;
