@@ -48,7 +48,7 @@ __device__ __forceinline__ double val(const T *a, long long o, long long lo_off)
 // Sums the workgroup's values over its threads, in red[][0].
 __device__ __forceinline__ void reduce(double (*red)[kBlock], const double *v)
 {
-    const int t = threadIdx.x;
+    const int t = threadIdx.y * blockDim.x + threadIdx.x;
     for (int q = 0; q < kQ; ++q) red[q][t] = v[q];
     __syncthreads();
     for (int s = kBlock / 2; s > 0; s >>= 1) {
@@ -62,13 +62,13 @@ __device__ __forceinline__ void reduce(double (*red)[kBlock], const double *v)
     }
 }
 
-// Workgroup b walks the runs b, b + kGrid, ... of kBlock nodes within a plane (the index of a run is
-// uniform, a node's row comes from a multiplication). What bounds it: the latency of a run's loads, which
-// are all in flight at once, and twelve FP64 divisions a node. 133 x 40 x 71, both media: 11.5 us, 22.4 with
+// Workgroup b walks the runs b, b + kGrid, ... of kBlock nodes within a plane, or within a few small planes
+// (the index of a run is uniform, a node's row comes from a multiplication). What bounds it: the latency of a
+// run's loads, which are all in flight at once, and twelve FP64 divisions a node. 133 x 40 x 71, both media: 11.5 us, 22.4 with
 // each load behind the test that needs it; 256^3 with the second kernel and the copy 291 us, 685 before. A
 // second small kernel adds up the partial results: doing that in the workgroup that finishes last needs a
 // fence in each of the 1024, and took 92 us when the two kernels took 28.
-template <typename T>
+template <typename T, typename Walk>
 __global__ void __launch_bounds__(kBlock)
     k_diag(Geom g, PlaneIndex ix, Fields<T> f, Coefs<typename Store<T>::C> c, double *partial)
 {
@@ -76,14 +76,16 @@ __global__ void __launch_bounds__(kBlock)
     const int nx = g.nx, ny = g.ny, nz = g.nz;
     const int X = nx + 1;
     const unsigned n = (unsigned)X * (unsigned)(ny + 1);
-    const unsigned runs = (n + kBlock - 1) / kBlock;  // of one plane
+    const unsigned runs = (n + Walk::width() - 1) / Walk::width();             // of one plane
+    const unsigned groups = ((unsigned)nz + Walk::planes()) / Walk::planes();  // of the nz + 1 planes
     const long long P = g.plane;
     const int px = g.px;
     double w = 0, se = 0, sh = 0, mdiv = 0, mtan = 0, bad = 0;
-    for (unsigned long long item = blockIdx.x; item < (unsigned long long)runs * (unsigned)(nz + 1); item += kGrid) {
-        const int k = (int)(item / runs);
-        const unsigned q0 = (unsigned)(item - (unsigned long long)k * runs) * kBlock + threadIdx.x;
-        if (q0 >= n)
+    for (unsigned long long item = blockIdx.x; item < (unsigned long long)runs * groups; item += kGrid) {
+        const unsigned z = (unsigned)(item / runs);
+        const int k = (int)(z * Walk::planes() + Walk::plane());
+        const unsigned q0 = (unsigned)(item - (unsigned long long)z * runs) * Walk::width() + threadIdx.x;
+        if (q0 >= n || (Walk::planes() > 1 && k > nz))
             continue;
         const int j = (int)ix.row(q0, X, nx), i = (int)q0 - j * X;
         const long long o = g.at(i, j, k);
@@ -148,8 +150,9 @@ __global__ void __launch_bounds__(kBlock)
     }
     const double own[kQ] = {w, se, sh, mdiv, mtan, bad};
     reduce(red, own);
-    if (threadIdx.x < kQ)
-        partial[(long long)blockIdx.x * kQ + threadIdx.x] = red[threadIdx.x][0];
+    const unsigned t = threadIdx.y * blockDim.x + threadIdx.x;
+    if (t < kQ)
+        partial[(long long)blockIdx.x * kQ + t] = red[t][0];
 }
 
 __global__ void __launch_bounds__(kBlock) k_diag_final(const double *partial, double *out)
@@ -175,7 +178,10 @@ template <typename T>
 hipError_t launch_diag(const Geom &g, const Fields<T> &f, const Coefs<typename Store<T>::C> &c, double *partial,
                        double *out_dev, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_diag<T>), dim3(kGrid), dim3(kBlock), 0, s, g, plane_index(g), f, c, partial);
+    by_walk(g, 1, [&](auto walk) {
+        hipLaunchKernelGGL((k_diag<T, decltype(walk)>), dim3(kGrid), plane_block(g, 1), 0, s, g, plane_index(g), f, c,
+                           partial);
+    });
     hipLaunchKernelGGL(k_diag_final, dim3(1), dim3(kBlock), 0, s, partial, out_dev);
     return hipGetLastError();
 }

@@ -31,18 +31,18 @@ struct InitOut {
     double scale[3];
 };
 
-// Component blockIdx.z, one thread per node of a plane (PlaneIndex), planes by blockIdx.y.
-template <typename T>
+// Component blockIdx.z, one thread per node of a plane (PlaneIndex), planes as plane_grid gives them.
+template <typename T, typename Walk>
 __global__ void __launch_bounds__(kBlock) k_init_random(Geom g, PlaneIndex ix, unsigned long long seed, InitOut<T> out)
 {
     const int field = blockIdx.z;
     int X, Y, Z;
     extents(g, field, X, Y, Z);
-    const unsigned n = (unsigned)X * (unsigned)Y, q = blockIdx.x * kBlock + threadIdx.x;
+    const unsigned n = (unsigned)X * (unsigned)Y, q = blockIdx.x * Walk::width() + threadIdx.x;
     if (q >= n)
         return;
     const int j = (int)ix.row(q, X, g.nx), i = (int)q - j * X;
-    for (int k = blockIdx.y; k < Z; k += gridDim.y) {
+    for (int k = Walk::first(); k < Z; k += Walk::step()) {
         const long long l = (long long)k * n + q;
         typename Store<T>::C v = 0;
         if (field < 3) {
@@ -79,7 +79,10 @@ hipError_t launch_init_random(const Geom &g, unsigned long long seed, T *const a
         out.b[f] = b[f];
     }
     for (int q = 0; q < 3; ++q) out.scale[q] = scale ? scale[q] : 1.0;
-    hipLaunchKernelGGL((k_init_random<T>), plane_grid(g, 6, 1), dim3(kBlock), 0, s, g, plane_index(g), seed, out);
+    by_walk(g, 1, [&](auto walk) {
+        hipLaunchKernelGGL((k_init_random<T, decltype(walk)>), plane_grid(g, 6, 1), plane_block(g, 1), 0, s, g,
+                           plane_index(g), seed, out);
+    });
     return hipGetLastError();
 }
 

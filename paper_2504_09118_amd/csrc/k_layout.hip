@@ -51,7 +51,7 @@ struct Boxes {
 // 4.4 TB/s), from 2.37 and 3.0 ms with a launch per component and 64-bit divisions per element; 16^3:
 // one launch instead of six (4 us each).
 // SCALED: rectangular cells; the cubic scale is exactly 1.
-template <typename S, typename T, bool SCALED>
+template <typename S, typename T, bool SCALED, typename Walk>
 __global__ void __launch_bounds__(kBlock) k_pack(Geom g, PlaneIndex ix, Boxes<const S, T> b, int f0)
 {
     const int f = f0 + blockIdx.z;
@@ -59,12 +59,12 @@ __global__ void __launch_bounds__(kBlock) k_pack(Geom g, PlaneIndex ix, Boxes<co
     extents(g, f, X, Y, Z);
     const unsigned n = (unsigned)X * (unsigned)Y;
     const double scale = b.scale[f % 3];
-    for (int k = blockIdx.y; k < Z; k += gridDim.y) {
+    for (int k = Walk::first(); k < Z; k += Walk::step()) {
         const S *src = b.dense[f] + (long long)k * n;
         const long long ok = (long long)k * g.plane;
 #pragma unroll
         for (int u = 0; u < kPlaneUnroll; ++u) {
-            const unsigned q = (blockIdx.x * kPlaneUnroll + u) * kBlock + threadIdx.x;
+            const unsigned q = (blockIdx.x * kPlaneUnroll + u) * Walk::width() + threadIdx.x;
             if (q >= n)
                 break;
             const int j = (int)ix.row(q, X, g.nx), i = (int)q - j * X;
@@ -84,7 +84,7 @@ __global__ void __launch_bounds__(kBlock) k_pack(Geom g, PlaneIndex ix, Boxes<co
     }
 }
 
-template <typename T, typename S, bool SCALED>
+template <typename T, typename S, bool SCALED, typename Walk>
 __global__ void __launch_bounds__(kBlock) k_unpack(Geom g, PlaneIndex ix, Boxes<S, const T> b, int f0)
 {
     const int f = f0 + blockIdx.z;
@@ -92,13 +92,13 @@ __global__ void __launch_bounds__(kBlock) k_unpack(Geom g, PlaneIndex ix, Boxes<
     extents(g, f, X, Y, Z);
     const unsigned n = (unsigned)X * (unsigned)Y;
     const double scale = b.scale[f % 3];
-    for (int k = blockIdx.y; k < Z; k += gridDim.y) {
+    for (int k = Walk::first(); k < Z; k += Walk::step()) {
         S *dst = b.dense[f] + (long long)k * n;
         const long long ok = (long long)k * g.plane;
         typename Store<T>::C v[kPlaneUnroll];
 #pragma unroll
         for (int u = 0; u < kPlaneUnroll; ++u) {
-            const unsigned q = (blockIdx.x * kPlaneUnroll + u) * kBlock + threadIdx.x;
+            const unsigned q = (blockIdx.x * kPlaneUnroll + u) * Walk::width() + threadIdx.x;
             if (q >= n)
                 break;
             const int j = (int)ix.row(q, X, g.nx), i = (int)q - j * X;
@@ -106,7 +106,7 @@ __global__ void __launch_bounds__(kBlock) k_unpack(Geom g, PlaneIndex ix, Boxes<
         }
 #pragma unroll
         for (int u = 0; u < kPlaneUnroll; ++u) {
-            const unsigned q = (blockIdx.x * kPlaneUnroll + u) * kBlock + threadIdx.x;
+            const unsigned q = (blockIdx.x * kPlaneUnroll + u) * Walk::width() + threadIdx.x;
             if (q < n)
                 dst[q] = SCALED ? (S)((double)v[u] / scale) : (S)v[u];
         }
@@ -124,18 +124,18 @@ struct CoefOut {
 };
 
 // One thread per node of component f0 + blockIdx.z (0..2 E edges, 3..5 H faces).
-template <typename T>
+template <typename T, typename Walk>
 __global__ void __launch_bounds__(kBlock) k_coef(Geom g, PlaneIndex ix, int f0, double dx, double dt,
                                                  const double *__restrict__ m, CoefOut co)
 {
     const int field = f0 + blockIdx.z;
     int X, Y, Z;
     extents(g, field, X, Y, Z);
-    const unsigned q = blockIdx.x * kBlock + threadIdx.x;
+    const unsigned q = blockIdx.x * Walk::width() + threadIdx.x;
     if (q >= (unsigned)X * (unsigned)Y)
         return;
     const int j = (int)ix.row(q, X, g.nx), i = (int)q - j * X;
-    for (int k = blockIdx.y; k < Z; k += gridDim.y) {
+    for (int k = Walk::first(); k < Z; k += Walk::step()) {
         const int nx = g.nx, ny = g.ny, nz = g.nz;
         double c = 0.0;
         switch (field) {
@@ -191,11 +191,13 @@ hipError_t launch_pack(const Geom &g, int f0, int nf, const S *const *src, T *co
     }
     const bool scaled = scale && (scale[0] != 1.0 || scale[1] != 1.0 || scale[2] != 1.0);
     for (int a = 0; a < 3; ++a) b.scale[a] = scale ? scale[a] : 1.0;
-    const dim3 grid = plane_grid(g, nf, kPlaneUnroll);
-    if (scaled)
-        hipLaunchKernelGGL((k_pack<S, T, true>), grid, dim3(kBlock), 0, s, g, plane_index(g), b, f0);
-    else
-        hipLaunchKernelGGL((k_pack<S, T, false>), grid, dim3(kBlock), 0, s, g, plane_index(g), b, f0);
+    const dim3 grid = plane_grid(g, nf, kPlaneUnroll), block = plane_block(g, kPlaneUnroll);
+    by_walk(g, kPlaneUnroll, [&](auto walk) {
+        if (scaled)
+            hipLaunchKernelGGL((k_pack<S, T, true, decltype(walk)>), grid, block, 0, s, g, plane_index(g), b, f0);
+        else
+            hipLaunchKernelGGL((k_pack<S, T, false, decltype(walk)>), grid, block, 0, s, g, plane_index(g), b, f0);
+    });
     return hipGetLastError();
 }
 
@@ -210,11 +212,13 @@ hipError_t launch_unpack(const Geom &g, int f0, int nf, const T *const *src, S *
     }
     const bool scaled = scale && (scale[0] != 1.0 || scale[1] != 1.0 || scale[2] != 1.0);
     for (int a = 0; a < 3; ++a) b.scale[a] = scale ? scale[a] : 1.0;
-    const dim3 grid = plane_grid(g, nf, kPlaneUnroll);
-    if (scaled)
-        hipLaunchKernelGGL((k_unpack<T, S, true>), grid, dim3(kBlock), 0, s, g, plane_index(g), b, f0);
-    else
-        hipLaunchKernelGGL((k_unpack<T, S, false>), grid, dim3(kBlock), 0, s, g, plane_index(g), b, f0);
+    const dim3 grid = plane_grid(g, nf, kPlaneUnroll), block = plane_block(g, kPlaneUnroll);
+    by_walk(g, kPlaneUnroll, [&](auto walk) {
+        if (scaled)
+            hipLaunchKernelGGL((k_unpack<T, S, true, decltype(walk)>), grid, block, 0, s, g, plane_index(g), b, f0);
+        else
+            hipLaunchKernelGGL((k_unpack<T, S, false, decltype(walk)>), grid, block, 0, s, g, plane_index(g), b, f0);
+    });
     return hipGetLastError();
 }
 
@@ -230,8 +234,10 @@ hipError_t launch_coef(const Geom &g, double dx, double dt, const double *eps, c
     for (int f0 = 0; f0 < 6; f0 += 3) {
         if (!co.out[f0])
             continue;
-        hipLaunchKernelGGL((k_coef<T>), plane_grid(g, 3, 1), dim3(kBlock), 0, s, g, plane_index(g), f0, dx, dt,
-                           f0 == 0 ? eps : mu, co);
+        by_walk(g, 1, [&](auto walk) {
+            hipLaunchKernelGGL((k_coef<T, decltype(walk)>), plane_grid(g, 3, 1), plane_block(g, 1), 0, s, g,
+                               plane_index(g), f0, dx, dt, f0 == 0 ? eps : mu, co);
+        });
         hipError_t e = hipGetLastError();
         if (e != hipSuccess)
             return e;
