@@ -501,16 +501,19 @@ int best_zsplit(long long tiles, int nz, int redo, int min_planes, int cus, int 
 {
     long long best = -1;
     int zc_best = 1;
-    for (int zc = 1; zc <= std::max(1, nz / min_planes); ++zc) {
+    const int most = std::max(1, nz / min_planes);
+    for (int zc = 1; zc <= most;) {  // each chunk length there is, with the fewest chunks
         const long long kc = (nz + zc - 1) / zc, nzc = (nz + kc - 1) / kc;
-        if (max_planes > 0 && kc > max_planes && zc < std::max(1, nz / min_planes))
-            continue;
-        const long long waves = (tiles * nzc + cus - 1) / cus;
-        const long long cost = waves * (kc + redo);
-        if (best < 0 || cost < best) {
-            best = cost;
-            zc_best = zc;
+        const int next = kc > 1 ? (int)((nz + kc - 2) / (kc - 1)) : most + 1;
+        if (max_planes <= 0 || kc <= max_planes || next > most) {
+            const long long waves = (tiles * nzc + cus - 1) / cus;
+            const long long cost = waves * (kc + redo);
+            if (best < 0 || cost < best) {
+                best = cost;
+                zc_best = zc;
+            }
         }
+        zc = next;
     }
     if (least)
         *least = best;
