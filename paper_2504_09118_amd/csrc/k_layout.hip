@@ -62,6 +62,15 @@ __global__ void __launch_bounds__(kBlock) k_pack(Geom g, PlaneIndex ix, Boxes<co
     for (int k = Walk::first(); k < Z; k += Walk::step()) {
         const S *src = b.dense[f] + (long long)k * n;
         const long long ok = (long long)k * g.plane;
+        // every load before the first store, which the compiler may not move them over
+        S in[kPlaneUnroll];
+#pragma unroll
+        for (int u = 0; u < kPlaneUnroll; ++u) {
+            const unsigned q = (blockIdx.x * kPlaneUnroll + u) * Walk::width() + threadIdx.x;
+            if (q >= n)
+                break;
+            in[u] = src[q];
+        }
 #pragma unroll
         for (int u = 0; u < kPlaneUnroll; ++u) {
             const unsigned q = (blockIdx.x * kPlaneUnroll + u) * Walk::width() + threadIdx.x;
@@ -69,7 +78,7 @@ __global__ void __launch_bounds__(kBlock) k_pack(Geom g, PlaneIndex ix, Boxes<co
                 break;
             const int j = (int)ix.row(q, X, g.nx), i = (int)q - j * X;
             // scaled in FP64; 16-bit storage: rounded to FP32, then to the 16-bit type
-            typename Store<T>::C v = to_compute<T>(SCALED ? (double)src[q] * scale : (double)src[q]);
+            typename Store<T>::C v = to_compute<T>(SCALED ? (double)in[u] * scale : (double)in[u]);
             if (e_wall(f, i, j, k, g.nx, g.ny, g.nz))
                 v = 0;
             // a wall-normal H of -0 is stored as +0 (equal values): sweeps that add the zero curl to
