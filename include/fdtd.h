@@ -348,8 +348,10 @@ int fdtd_destroy(fdtd_t h);
  * the probes; a reverse sweep is fused (mu' = mu - K(Ce lam), the gradient
  * terms, lam' = lam - L(Ch mu'), the probe terms) from one adjoint buffer to
  * the other. With FP32 storage and up to 64 probes sweeps are in column form:
- * up to four steps forward, up to two in reverse (scalar Ch); else slab sweeps
- * of one step (up to 16 probes ride in them, a probe kernel takes more).
+ * up to four steps forward, up to two in reverse (scalar Ch); else, and for a
+ * forward step left alone between checkpoints of a state larger than the
+ * last-level cache, slab sweeps of one step (up to 16 probes ride in them, a
+ * probe kernel takes more).
  * Environment aids (none changes the bits): FDTD_ADJ_FUSED = 0 (the
  * one-cell-per-thread reverse kernels, in place); for the slab form of the
  * reverse sweep FDTD_ADJ_VARIANT = 0..3 (tile shape; default 1) and

@@ -3,7 +3,8 @@
 //
 // Forward: N leapfrog steps of the solver, each followed by the point
 // source and the probe reads, up to four of them in one column sweep (FP32
-// storage and at most 64 probes; else a slab sweep each); the state
+// storage and at most 64 probes; else, and for a step left alone in a state
+// that streams from HBM, a slab sweep each); the state
 // (E^n, H^{n-1/2}) is copied to a checkpoint every K steps; the steps of the last segment write each H^{n+1/2}
 // straight into a history slot. Backward: for each segment of K steps, last
 // one first, the segment is recomputed from its checkpoint into the history
@@ -223,6 +224,11 @@ int driven_steps(const fdtd_adjoint *a, long long left)
     return left >= a->ts_fwd ? a->ts_fwd : left >= 2 ? 2 : 1;
 }
 
+// A single driven step of a state that streams from HBM (a checkpoint after every step, or an odd number of
+// steps between them) is a slab sweep: 24 steps of 256^3 with their checkpoints 9.9 ms, 12.1 in columns; 192^3 4.65
+// and 5.1; from the last-level cache columns are ahead (128^3 1.75 and 1.64, 64^3 0.66 of the slabs' time).
+bool single_in_slabs(const fdtd_adjoint *a, int ts) { return ts == 1 && a->s->nt_stores; }
+
 // The forward in column sweeps of at most 4 steps that end at the checkpoints. In the last segment every
 // H^{n+1/2} goes to its slot; a sweep's last one is also the next sweep's H input, so only the pass's last
 // sweep writes the solver's own H.
@@ -236,6 +242,18 @@ int forward_columns(fdtd_adjoint_t a)
             return fdtd::solver_device_fail(s, e, "checkpoint");
         const int ts = driven_steps(a, std::min<long long>(a->K - n % a->K, a->N - n));
         const bool held = n >= nl, last = n + ts == a->N;
+        if (single_in_slabs(a, ts) && !(held && last)) {  // (the last one writes its slot and the solver's H)
+            float *hin[3] = {}, *hout[3] = {};
+            for (int f = 0; f < 3 && held; ++f) {
+                hin[f] = n > nl ? hist_slot<float>(a, n - nl - 1, f) : nullptr;
+                hout[f] = hist_slot<float>(a, n - nl, f);
+            }
+            if (int st = driven_step<float>(a, n, a->d_rec + (size_t)(n + 1) * a->np, held && n > nl ? hin : nullptr,
+                                            held ? hout : nullptr))
+                return st;
+            n += 1;
+            continue;
+        }
         Fields<float> src = state_of<float>(s), dst = other_of<float>(s);
         for (int f = 0; f < 3 && held; ++f) {
             if (n > nl)
@@ -362,7 +380,12 @@ int backward_impl(fdtd_adjoint_t a, double *grad, void *const lam0[3], int lam0_
                     src.f[3 + f] = n == n0 ? (float *)s->fld[b][3 + f] : slot_h(n - n0 - 1, f);
                     dst.f[3 + f] = slot_h(n - n0 + ts - 1, f);
                 }
-                e = driven_sweep(a, src, dst, n, ts, nullptr, slot_h(n - n0, 0), ts - 1);
+                if (single_in_slabs(a, ts)) {
+                    const fdtd::SlabExtras x = extras_of(a, n, nullptr);
+                    e = fdtd::launch_slab_step<float>(g, src, dst, c, s->zchunk, s->variant, s->stream, true, &x);
+                } else {
+                    e = driven_sweep(a, src, dst, n, ts, nullptr, slot_h(n - n0, 0), ts - 1);
+                }
                 if (e != hipSuccess)
                     return fdtd::solver_device_fail(s, e, "recompute sweep");
                 b = 1 - b;
@@ -577,8 +600,8 @@ int fdtd_adjoint_create(fdtd_t s, const fdtd_adjoint_problem *p, fdtd_adjoint_t 
     const size_t o_po = off;
     off += up((size_t)std::max(1, a->np) * sizeof(long long));
     // column sweeps at every size (both passes of 48x40x56 take 0.4 of the slab sweeps' time, of 128^3 0.85,
-    // of 384^3 0.9), where a plane's byte offsets fit 31 bits; the reverse one for one scalar Ch
-    a->fwd_column = s->storage == FDTD_F32 && a->np <= fdtd::kColumnProbes && g.plane < (1LL << 29);
+    // of 384^3 0.9; a plane's byte offsets fit 31 bits in every solver); the reverse one for one scalar Ch
+    a->fwd_column = s->storage == FDTD_F32 && a->np <= fdtd::kColumnProbes;
     a->rev_column = a->fwd_column && !s->ch_arr;
     const size_t o_tab = off;
     off += up(sizeof(fdtd::DriveTable));
