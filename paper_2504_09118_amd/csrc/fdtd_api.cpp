@@ -387,14 +387,20 @@ hipError_t unpack_all(fdtd_t h, void *const dst[6], bool staged, void *const *bo
         all = all && boxes[f];
     }
     const double *scale = scaled ? h->scale : nullptr;
-    if (!staged && all)
-        return fdtd::launch_unpack<T, S>(h->plan.g, 0, 6, src, out, h->stream, scale);
     size_t bytes[6];
     for (int f = 0; f < 6; ++f) {
         int X, Y, Z;
         fdtd::extents(h->plan.g, f, X, Y, Z);
         bytes[f] = (size_t)X * Y * Z * sizeof(S);
     }
+    // arrays that overlap (one buffer for several that are not wanted) hold the last of their components
+    bool apart = true;
+    for (int f = 0; f < 6; ++f)
+        for (int q = 0; q < f; ++q)
+            apart = apart && ((uintptr_t)dst[f] >= (uintptr_t)dst[q] + bytes[q] ||
+                              (uintptr_t)dst[q] >= (uintptr_t)dst[f] + bytes[f]);
+    if (!staged && all && apart)
+        return fdtd::launch_unpack<T, S>(h->plan.g, 0, 6, src, out, h->stream, scale);
     hipError_t e = hipSuccess;
     if (staged)
         h->reader.begin(h->device, h->stream, 6, *std::max_element(bytes, bytes + 6));
