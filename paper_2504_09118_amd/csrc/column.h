@@ -31,6 +31,7 @@
 
 #include <type_traits>
 
+#include "column_lanes.h"
 #include "fdtd_internal.h"
 #include "storage.h"
 #include "tile_queue.h"
@@ -73,25 +74,6 @@ struct FieldBoxes {
     __device__ __forceinline__ float scalar_ce() const { return c.ce_s; }
     __device__ __forceinline__ float scalar_ch() const { return c.ch_s; }
 };
-
-constexpr unsigned kDrop = 0x80000000u;      // an offset past every plane: reads 0, stores nothing
-constexpr int kRawBufferWord3 = 0x00020000;  // gfx9 raw buffer: 32-bit data format, no swizzle
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_rsrc(const void *p, unsigned bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, kRawBufferWord3);
-}
-
-// Value of the lane one column to the right / left; 0 at the window's edge (every lane is active).
-__device__ __forceinline__ float right_of(float x)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x130, 0xf, 0xf, true));
-}
-
-__device__ __forceinline__ float left_of(float x)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x138, 0xf, 0xf, true));
-}
 
 template <typename S, int TS, bool CE_ARR, bool CH_ARR, int kNW, typename Boxes, typename Drive>
 __device__ __forceinline__ void column_tile(const Geom &g, const Boxes &b, int kchunk, int ntx, int nty,
@@ -173,8 +155,8 @@ __device__ __forceinline__ void column_tile(const Geom &g, const Boxes &b, int k
                 RC[m][q][r] = CE_ARR ? 0.0f : b.scalar_ce();
                 RK[m][q][r] = CH_ARR ? 0.0f : b.scalar_ch();
             }
-#define ES(r, ph) ((((r) + 2 + (ph)) % M + M) % M)
-#define HS(r, ph) ((((r) + 1 + (ph)) % M + M) % M)
+#define ES(r, ph) ring_slot(r, ph, 2, M)
+#define HS(r, ph) ring_slot(r, ph, 1, M)
     const int k0 = max(0, kb - TS), kend = ke + TS - 2;
     const unsigned fbytes = (unsigned)(P * (long long)sizeof(S)), cbytes = (unsigned)(P * 4);
 

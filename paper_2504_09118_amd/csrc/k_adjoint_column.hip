@@ -12,6 +12,7 @@
 // three barriers and its scalar address work keep it from the 11 TB/s that a copy there reaches. A sweep of
 // one step takes 71 us. 128^3, 200 steps with 2 probes: 8.7 ms, slab sweeps 10.0; 48x40x56, 150 steps:
 // 1.06 (narrow workgroups; 1.28 full) and 2.2 ms.
+#include "column_lanes.h"
 #include "fdtd_internal.h"
 #include "tile_queue.h"
 #include "yee_update.h"
@@ -22,25 +23,8 @@ namespace fdtd {
 namespace {
 
 constexpr int kNR = kColumnRows, kCols = 64;
-constexpr unsigned kDrop = 0x80000000u;
-constexpr int kRawBufferWord3 = 0x00020000;
 
 __device__ __forceinline__ float rmul(float a, float b) { return a * b; }
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_rsrc(const void *p, unsigned bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, kRawBufferWord3);
-}
-
-__device__ __forceinline__ float right_of(float x)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x130, 0xf, 0xf, true));
-}
-
-__device__ __forceinline__ float left_of(float x)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x138, 0xf, 0xf, true));
-}
 
 template <int TS, int kNW>
 __global__ void __launch_bounds__(64 * kNW, (kNW != kNarrowWaves ? 1 : adjoint_narrow_pairs(TS) ? 4 : 2))
@@ -118,8 +102,8 @@ __global__ void __launch_bounds__(64 * kNW, (kNW != kNarrowWaves ? 1 : adjoint_n
                     hp[s][q][r] = 0.0f;
             }
         }
-#define ES(r, ph) ((((r) + 2 + (ph)) % M + M) % M)
-#define HS(r, ph) ((((r) + 1 + (ph)) % M + M) % M)
+#define ES(r, ph) ring_slot(r, ph, 2, M)
+#define HS(r, ph) ring_slot(r, ph, 1, M)
     const int k0 = max(0, kb - TS), kend = ke + TS - 2;
     const unsigned bytes = (unsigned)(P * 4);
     const float ch = b.ch_s, m1 = -1.0f;
