@@ -51,7 +51,7 @@ struct Shared {
     PinnedSlots *idle[kSlotSets] = {};
     int nidle = 0;
 };
-constexpr size_t kWorth = 32 << 20, kLeast = 4 << 20, kLeastOne = 512 << 10;
+constexpr size_t kWorth = 32 << 20, kLeastOne = 512 << 10;
 constexpr int kDevices = 64;
 Shared g_shared[kDevices];
 std::mutex g_mu;
@@ -154,8 +154,10 @@ void HostReader::begin(int device, hipStream_t s, int n, size_t largest)
     n_ = n;
     largest_ = largest;
     slots_ = nullptr;
-    // a small read is left to the runtime: a solver that read 1.7 MB in slots ends 50 us later, all it gained
-    tried_ = (size_t)n * largest < (n == 1 ? kLeastOne : kLeast);
+    // one small array is left to the runtime (0.2 MB: 65 us of a gradient, 80 in slots; 0.9 MB in fresh pages 0.5
+    // ms and 0.2); six are not, whatever their size: they arrive in 89 us, not 146 (16^3 and below), 48^3 in
+    // 210, not 255, and the solver's end takes 10 to 30 us more
+    tried_ = n == 1 && largest < kLeastOne;
     closed_ = false;
     lo_ = hi_ = nullptr;
     pending_ = 0;

@@ -116,7 +116,7 @@ static void known_memory_makes_no_slots()
     CHECK(fake::allocations == 0);
 }
 
-// Slots wait until the objects together have read enough, and the smallest reads do without.
+// Slots wait until the objects together have read enough, by reads of any size; one small array does without.
 static void small_reads()
 {
     for (int q = 0; q < 3; ++q) {
@@ -128,10 +128,13 @@ static void small_reads()
         HostReader r;
         CHECK(read(r, 6, MiB / 2) == hipSuccess);
     }
-    CHECK(fake::allocations == 0);
-    HostReader r;
-    CHECK(read(r, 6, MiB) == hipSuccess);
     CHECK(fake::allocations == 1);
+    HostReader r;
+    int copies = fake::runtime_copies;
+    CHECK(read(r, 6, 100) == hipSuccess);
+    CHECK(fake::allocations == 1 && fake::runtime_copies == copies);
+    CHECK(read(r, 1, MiB / 4) == hipSuccess);
+    CHECK(fake::allocations == 1 && fake::runtime_copies == copies + 1);
 }
 
 // Slots are filled by the kernel, whatever the sizes; a source off its 16-byte boundary is the runtime's.
