@@ -165,8 +165,9 @@ int fdtd_required_bytes(int nx, int ny, int nz, const fdtd_coef *coef, const fdt
  * Environment overrides read here (tuning and test aids; none changes the
  * bits): FDTD_ZCHUNKS and FDTD_SLAB_VARIANT (fused / slab z-split and tile
  * shape), FDTD_TZCHUNKS and FDTD_TEMPORAL_VARIANT (temporal sweep),
- * FDTD_NT_STORES = 0 / 1 (store policy; default: non-temporal when one sweep
- * streams more than 256 MB), FDTD_XCD_REMAP = 0 / 1 / 2 (workgroup-to-tile
+ * FDTD_NT_STORES = 0 / 1 (store policy and form of the sweeps; default:
+ * non-temporal when one sweep streams more than 256 MB; 0 gives every temporal
+ * sweep the column form), FDTD_XCD_REMAP = 0 / 1 / 2 (workgroup-to-tile
  * order, read once per process: launch order; one contiguous block of tiles
  * per XCD; default 2, the temporal sweeps' resident workgroups covering one
  * contiguous tile range, which the slab sweeps treat as 1),
@@ -174,7 +175,7 @@ int fdtd_required_bytes(int nx, int ny, int nz, const fdtd_coef *coef, const fdt
  * workgroup per tile in the FDTD_XCD_REMAP order; default 1, one workgroup per
  * CU taking tiles from a queue; a sweep of a state that the last-level cache
  * holds, the one FDTD_NT_STORES chooses, takes one workgroup per tile when
- * every tile has a CU of its own).
+ * every tile has a CU of its own or workgroups are of 8 waves).
  */
 int fdtd_create(int nx, int ny, int nz, double dx, double dt, const fdtd_coef *coef,
                 const fdtd_opts *opts, fdtd_t *out);

@@ -2,8 +2,8 @@
 // the plane lag between them and the arithmetic of k_temporal.hip, hence the same bits, but another
 // split of the tile.
 //
-// A workgroup's window is 64 columns x 32 rows. A lane holds one column of kNR rows, a wave kNR
-// whole rows of the window, so
+// A workgroup's window is 64 columns x 32 rows, 24 or 16 where it has 12 or 8 waves. A lane holds one
+// column of kNR rows, a wave kNR whole rows of the window, so
 //   - the x neighbours of a cell are in the next lanes of the same wave: the differences read them
 //     by a wave shift inside the subtraction (a DPP operand), without LDS and without an extra
 //     instruction; a lane at the window's edge reads 0 there;
@@ -16,15 +16,16 @@
 // the outermost windows own up to the walls.
 //
 // What bounds it: neither HBM nor the matrix cores (there is no contraction). On a 128^3 cavity with
-// per-node Ce (a state the 256 MB last-level cache holds) a 4-step sweep takes 46 us: 15 planes of
-// about 2.7 us, in which the vector units are 40 % busy, the barriers and the chain of dependent
+// per-node Ce (a state the 256 MB last-level cache holds) a 4-step sweep takes 48 us: 15 planes of
+// about 2.8 us, in which the vector units are 40 % busy, the barriers and the chain of dependent
 // stages taking the rest; it moves 200 MB past L2, where that cache delivers 11 TB/s (18 us). The form
 // of k_temporal.hip, whose cells exchange 52 bytes a stage through LDS where these exchange 16, takes
-// 64 us on the same sweep. 64^3: 22 us (39 us). 16-bit storage, 128^3: FP16 49 us (57), BF16 with
-// residuals 67 us (74). Per-node Ce and Ch, 160 x 96 x 128, 3 steps: 43 us (62).
+// 68 us on the same sweep. 64^3: 18 us (58). 16-bit storage, 128^3: FP16 44 us (61), BF16 with
+// residuals 59 us (79). Per-node Ce and Ch, 160 x 96 x 128, 3 steps: 42 us (61).
 // Larger states keep the other form: there the sweep is bound by what memory serves, and windows whose
 // own cells do not end on 128-byte lines make two workgroups write parts of one line (512^3: 2.65 ms
-// against 2.08).
+// against 2.08; BF16 with residuals 320^3 0.63 against 0.55, FP16 0.46 and 0.41; FP16 at 394x301x350, whose
+// rows and planes divide badly among the other form's tiles, 0.60 and 0.65).
 #pragma once
 
 #include <algorithm>
@@ -521,7 +522,8 @@ hipError_t launch_column(const Geom &g, const Fields<S> &src, const Fields<S> &d
         column_windows(g.nx, g.ny, TS, waves, &ntx, &nty);
         const int ntiles = ntx * nty * nzc, nvb = (ntiles + kXcds - 1) / kXcds * kXcds;
         // with a CU for every tile there is nothing to hand out: a workgroup per tile saves the queue's
-        // serial atomics (64^3: 27 us a sweep through the queue, 24 without); narrow workgroups are two a CU
+        // serial atomics (64^3: 27 us a sweep through the queue, 24 without); narrow workgroups are handed out by the
+        // dispatcher, two a CU where their registers allow it
         const bool direct = !queue || temporal_sched() == 0 || ntiles <= kXcds * cpx || waves == kNarrowWaves;
         const dim3 block(64, waves), grid(direct ? nvb : std::min(ntiles, kXcds * cpx));
         hipLaunchKernelGGL(kernel, grid, block, 0, s, g, FieldBoxes<S>{src, dst, c}, kchunk, ntx, nty, ntiles, nvb,

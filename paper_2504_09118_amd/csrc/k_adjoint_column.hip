@@ -7,9 +7,9 @@
 // FP32 group sums of gCe cross memory once for TS steps. Products are rounded on their own and every
 // operand is that of k_adj_slab: the same bits.
 //
-// What bounds it: at 128^3 (two steps, 75 us; the slab sweep 43 us for one) 310 MB cross the last-level
-// cache's edge at 4.1 TB/s, the window's halo among them (60 of 64 columns, 20 of 24 rows own); a plane's
-// three barriers and its scalar address work keep it from the 11 TB/s that a copy there reaches. A sweep of
+// What bounds it: at 128^3 (two steps, 81 us; the slab sweep 43 us for one) 310 MB cross the last-level
+// cache's edge at 3.8 TB/s, the window's halo among them (60 of 64 columns, 20 of 24 rows own); a plane's
+// two barriers and its scalar address work keep it from the 11 TB/s that a copy there reaches. A sweep of
 // one step takes 71 us. 128^3, 200 steps with 2 probes: 8.7 ms, slab sweeps 10.0; 48x40x56, 150 steps:
 // 1.06 (narrow workgroups; 1.28 full) and 2.2 ms.
 #include "column_lanes.h"

@@ -2,7 +2,7 @@
 // step adds the point source to its E node, the probes record E after it, and H^{n+1/2} of every step
 // goes to its history slot; the state crosses memory once per launch.
 // What bounds it: at 128^3 the history (25 MB per step written once) and a plane's chain of barriers;
-// 200 steps with 2 probes take 3.85 ms, 27 us per single slab sweep before (5.4 ms). 48x40x56, 150 steps in
+// 200 steps with 2 probes take 3.9 ms, 27 us per single slab sweep before (5.4 ms). 48x40x56, 150 steps in
 // narrow workgroups: 0.74 ms, in full ones 0.97, slab sweeps 2.1.
 #include "column.h"
 

@@ -65,7 +65,7 @@ __device__ __forceinline__ void reduce(double (*red)[kBlock], const double *v)
 // Workgroup b walks the runs b, b + kGrid, ... of kBlock nodes within a plane, or within a few small planes
 // (the index of a run is uniform, a node's row comes from a multiplication). What bounds it: the latency of a
 // run's loads, which are all in flight at once, and twelve FP64 divisions a node. 133 x 40 x 71, both media: 11.5 us, 22.4 with
-// each load behind the test that needs it; 256^3 with the second kernel and the copy 291 us, 685 before. A
+// each load behind the test that needs it; 256^3 with the second kernel and the copy 244 us, 685 before. A
 // second small kernel adds up the partial results: doing that in the workgroup that finishes last needs a
 // fence in each of the 1024, and took 92 us when the two kernels took 28.
 template <typename T, typename Walk>

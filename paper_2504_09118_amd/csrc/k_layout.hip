@@ -47,8 +47,8 @@ struct Boxes {
 
 // A plane of a component is contiguous in the dense array, so a workgroup takes a run of it: one launch
 // for all components, an index by 32-bit multiplication instead of 64-bit divisions per element.
-// Bound by HBM: 512^3 FP32, six components: unpack 1.12 ms (6.45 GB: 5.8 TB/s), pack 2.21 ms (9.7 GB,
-// 4.4 TB/s), from 2.37 and 3.0 ms with a launch per component and 64-bit divisions per element; 16^3:
+// Bound by HBM: 512^3 FP32, six components: unpack 1.12 ms (6.45 GB: 5.8 TB/s), pack 1.94 ms (9.7 GB,
+// 5.0 TB/s), from 2.37 and 3.0 ms with a launch per component and 64-bit divisions per element; 16^3:
 // one launch instead of six (4 us each).
 // SCALED: rectangular cells; the cubic scale is exactly 1.
 template <typename S, typename T, bool SCALED, typename Walk>
