@@ -34,14 +34,16 @@ inline PlaneIndex plane_index(const Geom &g)
     return PlaneIndex{{fast_div((unsigned)g.nx), fast_div((unsigned)g.nx + 1)}};
 }
 
-// A workgroup's threads: runs of a plane by planes. Planes of a few nodes (long thin cavities) share a workgroup;
-// with one each, most of its threads are idle (2x2x50000 FP32: unpack 131 us, 18 so; diagnostics 105 and 46;
-// 4x4x20000 55 and 15, 58 and 41).
+// A workgroup's threads: runs of a plane by planes. Many planes of a few nodes (long thin cavities) share
+// workgroups; with one each, most threads are idle (2x2x50000 FP32: unpack 131 us, 18 so; diagnostics 105 and 46;
+// 4x4x20000 55 and 15, 58 and 41; 12x12x400 3.5 and 3.3). Fewer planes fill the chip as they are (10x10x200 2.9 us,
+// shared 3.2; 16^3 2.6 and 3.1).
+constexpr int kManyPlanes = 512;
 inline dim3 plane_block(const Geom &g, int unroll)
 {
     const long long n = (long long)(g.nx + 1) * (g.ny + 1);
     unsigned w = kPlaneBlock;
-    while (w > 1 && (long long)(w / 2) * unroll >= n) w /= 2;
+    while (g.nz >= kManyPlanes && w > 1 && (long long)(w / 2) * unroll >= n) w /= 2;
     return dim3(w, kPlaneBlock / w);
 }
 

@@ -1,7 +1,7 @@
 """Long thin cavities, whose planes share a workgroup: layout, seeded state, coefficients, diagnostics.
 
-Planes of 9 to 306 nodes about the powers of two at which the workgroup's shape changes, and numbers of
-planes that its planes do not divide. Copies are exact; the sums differ from the oracle's by the order of
+Planes of 9 to 342 nodes about the powers of two at which the workgroup's shape changes, numbers of
+planes that its planes do not divide, and cavities just too short for it (511 cells). Copies are exact; the sums differ from the oracle's by the order of
 their N terms only: 8 N 2^-53.
 """
 
@@ -14,8 +14,8 @@ from tests.test_gpu_layout import close_walls
 
 pytestmark = pytest.mark.gpu
 
-DIMS = [(2, 2, 700), (3, 3, 65), (4, 2, 127), (7, 7, 2001), (7, 8, 30), (10, 11, 63), (15, 15, 50), (16, 15, 131),
-        (17, 16, 9)]
+DIMS = [(2, 2, 700), (3, 3, 565), (4, 2, 627), (7, 7, 2001), (7, 8, 530), (10, 11, 563), (15, 15, 550), (16, 15, 631),
+        (17, 16, 512), (18, 17, 517), (17, 16, 511), (2, 2, 511)]
 
 
 @pytest.mark.parametrize("storage", ["f32", "f64"])
