@@ -51,7 +51,7 @@ struct Shared {
     PinnedSlots *idle[kSlotSets] = {};
     int nidle = 0;
 };
-constexpr size_t kWorth = 32 << 20, kLeastOne = 512 << 10;
+constexpr size_t kWorth = 32 << 20;
 constexpr int kDevices = 64;
 Shared g_shared[kDevices];
 std::mutex g_mu;
@@ -88,7 +88,9 @@ PinnedSlots *create(size_t slot, int slots)
 // Slots for a read of n arrays of at most largest bytes, or null: the runtime copies. Making them takes one
 // to two milliseconds and saves 27 us for a MiB in mapped pages, more in fresh ones, so the first set waits
 // until kWorth has been read, the next ones (readers at the same time) for as much each. One array alone is
-// worth a set of its size at once (0.9 MiB in fresh pages: 0.5 ms by the runtime, 0.2).
+// worth a set of its size at once (0.9 MiB in fresh pages: 0.5 ms by the runtime, 0.2). A set there is serves
+// every size: six arrays of 16^3 or less arrive in 70 to 90 us, not 146, of 48^3 in 140, not 255; a gradient
+// of 24^3 by 24 steps takes 180, not 249.
 PinnedSlots *lease(int device, int n, size_t largest)
 {
     size_t slot = std::min(kSlot, (largest + 4095) / 4096 * 4096);
@@ -154,10 +156,7 @@ void HostReader::begin(int device, hipStream_t s, int n, size_t largest)
     n_ = n;
     largest_ = largest;
     slots_ = nullptr;
-    // one small array is left to the runtime (0.2 MB: 65 us of a gradient, 80 in slots; 0.9 MB in fresh pages 0.5
-    // ms and 0.2); six are not, whatever their size: they arrive in 89 us, not 146 (16^3 and below), 48^3 in
-    // 210, not 255, and the solver's end takes 10 to 30 us more
-    tried_ = n == 1 && largest < kLeastOne;
+    tried_ = false;
     closed_ = false;
     lo_ = hi_ = nullptr;
     pending_ = 0;
@@ -284,9 +283,10 @@ hipError_t HostReader::finish()
     cv_.wait(lk, [&] { return done_ == issued_; });
     lk.unlock();
     for (; nthreads_ > 0; --nthreads_) thread_[nthreads_ - 1].join();
-    // Nothing enqueued here outlives the call; where that is not known the slots are not used again. (With the
-    // events alone waited for, the stream's next wait or its end takes 30 to 150 us more.)
-    const hipError_t e = slots_ || err_ != hipSuccess ? hipStreamSynchronize(stream_) : hipSuccess;
+    // Every event has been waited for, so nothing enqueued here outlives the call; after an error the stream is,
+    // and where that fails the slots are not used again. (A wait for the stream each time costs 30 us a read: it
+    // has a marker of its own to send; without it the solver's end pays them once.)
+    const hipError_t e = err_ != hipSuccess ? hipStreamSynchronize(stream_) : hipSuccess;
     if (slots_ && e == hipSuccess) {
         std::lock_guard<std::mutex> shared_lk(g_mu);
         Shared &sh = g_shared[device_];
